@@ -227,14 +227,18 @@ __global__ __launch_bounds__(256) void expert_dot_kernel(DotArgs a) {
   }
 }
 
-// The batch's v row loads are guarded (a slot past the end loads nothing), and with guarded loads
-// the compiler waits for each row before issuing the next, so a wave fetches its rows one after
-// another. Unguarded loads with all eight rows in flight (as in accumulate_slots_kernel) were
-// slower here at the training shape, 1.44 -> 1.50 ms, and so were two or four rows in flight.
-template <int CPL, bool BF16>
+// DEEP = 0: the batch's v row loads are guarded (a slot past the end loads nothing), and with
+// guarded loads the compiler waits for each row before issuing the next, so a wave fetches its rows
+// one after another. With several waves per SIMD that is the fastest form (training shape: 1.44 ms
+// against 1.46-1.50 ms with two to eight rows in flight). DEEP > 0: DEEP rows of a wave in flight,
+// unguarded (past the last slot its row is loaded again and not added), for launches of about one
+// wave per SIMD, which one row in flight leaves waiting on latency (kAccDeepMaxRows below).
+// FULL: the wave's column split is exactly CPL * 64 chunks (DEEP > 0 only). The sum runs in slot
+// order in every form, so y is the same.
+template <int CPL, bool BF16, int DEEP, bool FULL>
 __global__ __launch_bounds__(256) void accumulate_kernel(AccArgs a) {
   constexpr int EPC = BF16 ? 8 : 4;
-  constexpr int UNROLL = CPL >= 16 ? 2 : (CPL >= 8 ? 4 : 8);
+  constexpr int UNROLL = DEEP > 0 ? DEEP : (CPL >= 16 ? 2 : (CPL >= 8 ? 4 : 8));
   const int l = lane_id();
   const uint4* V = (const uint4*)a.v;
   const int64_t row_chunks = a.nchunks;
@@ -245,12 +249,33 @@ __global__ __launch_bounds__(256) void accumulate_kernel(AccArgs a) {
     const int cbase = (int)(wt % a.splits) * CPL * kWave;  // first chunk of this wave
     bool cvalid[CPL];
 #pragma unroll
-    for (int q = 0; q < CPL; ++q) cvalid[q] = (cbase + l + kWave * q) < a.nchunks;
+    for (int q = 0; q < CPL; ++q) cvalid[q] = FULL || (cbase + l + kWave * q) < a.nchunks;
     float acc[CPL][EPC];
 #pragma unroll
     for (int q = 0; q < CPL; ++q)
 #pragma unroll
       for (int k = 0; k < EPC; ++k) acc[q][k] = 0.0f;
+    auto add = [&](float w, const uint4 (&row)[CPL]) {
+#pragma unroll
+      for (int q = 0; q < CPL; ++q) {
+        const uint4 c = row[q];
+        if constexpr (BF16) {
+          acc[q][0] = fmaf(w, bf16_lo(c.x), acc[q][0]);
+          acc[q][1] = fmaf(w, bf16_hi(c.x), acc[q][1]);
+          acc[q][2] = fmaf(w, bf16_lo(c.y), acc[q][2]);
+          acc[q][3] = fmaf(w, bf16_hi(c.y), acc[q][3]);
+          acc[q][4] = fmaf(w, bf16_lo(c.z), acc[q][4]);
+          acc[q][5] = fmaf(w, bf16_hi(c.z), acc[q][5]);
+          acc[q][6] = fmaf(w, bf16_lo(c.w), acc[q][6]);
+          acc[q][7] = fmaf(w, bf16_hi(c.w), acc[q][7]);
+        } else {
+          acc[q][0] = fmaf(w, __uint_as_float(c.x), acc[q][0]);
+          acc[q][1] = fmaf(w, __uint_as_float(c.y), acc[q][1]);
+          acc[q][2] = fmaf(w, __uint_as_float(c.z), acc[q][2]);
+          acc[q][3] = fmaf(w, __uint_as_float(c.w), acc[q][3]);
+        }
+      }
+    };
     for (int sb = 0; sb < a.hk; sb += kWave) {
       const int sl = sb + l;
       const bool valid = sl < a.hk;
@@ -261,39 +286,18 @@ __global__ __launch_bounds__(256) void accumulate_kernel(AccArgs a) {
         uint4 vr[UNROLL][CPL];
 #pragma unroll
         for (int u = 0; u < UNROLL; ++u) {
-          if (j + u < n) {
-            const int e = readlane_i32(ev, j + u);
+          if (DEEP > 0 || j + u < n) {
+            const int e = readlane_i32(ev, j + u < n ? j + u : n - 1);
             const uint4* vb = V + (int64_t)e * row_chunks + cbase;
 #pragma unroll
             for (int q = 0; q < CPL; ++q)
               vr[u][q] = cvalid[q] ? vb[l + kWave * q] : make_uint4(0, 0, 0, 0);
           }
         }
+        if constexpr (DEEP > 0) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int u = 0; u < UNROLL; ++u) {
-          if (j + u < n) {
-            const float w = readlane_f32(av, j + u);
-#pragma unroll
-            for (int q = 0; q < CPL; ++q) {
-              const uint4 c = vr[u][q];
-              if constexpr (BF16) {
-                acc[q][0] = fmaf(w, bf16_lo(c.x), acc[q][0]);
-                acc[q][1] = fmaf(w, bf16_hi(c.x), acc[q][1]);
-                acc[q][2] = fmaf(w, bf16_lo(c.y), acc[q][2]);
-                acc[q][3] = fmaf(w, bf16_hi(c.y), acc[q][3]);
-                acc[q][4] = fmaf(w, bf16_lo(c.z), acc[q][4]);
-                acc[q][5] = fmaf(w, bf16_hi(c.z), acc[q][5]);
-                acc[q][6] = fmaf(w, bf16_lo(c.w), acc[q][6]);
-                acc[q][7] = fmaf(w, bf16_hi(c.w), acc[q][7]);
-              } else {
-                acc[q][0] = fmaf(w, __uint_as_float(c.x), acc[q][0]);
-                acc[q][1] = fmaf(w, __uint_as_float(c.y), acc[q][1]);
-                acc[q][2] = fmaf(w, __uint_as_float(c.z), acc[q][2]);
-                acc[q][3] = fmaf(w, __uint_as_float(c.w), acc[q][3]);
-              }
-            }
-          }
-        }
+        for (int u = 0; u < UNROLL; ++u)
+          if (j + u < n) add(readlane_f32(av, j + u), vr[u]);
       }
     }
     // y is written once and not read back here: non-temporal stores keep it out of the caches
@@ -797,14 +801,37 @@ hipError_t dispatch_acc_slots(int cpl, int hk, dim3 grid, hipStream_t st, const 
   return hipGetLastError();
 }
 
+// Rows of 64 chunks (1 KiB) up to which a wave of accumulate_kernel keeps four v rows in flight:
+// T times the rows of a v row, i.e. four rows of 64 chunks per SIMD. Measured, dot and routed sum,
+// guarded against four rows in flight: d = 2048 (four) 509 tokens 113 -> 90 us, 1024 tokens 188 ->
+// 183, 2048 tokens 360 -> 363; d = 1024 (two), K = 512: 512 tokens 258 -> 175, 1024 tokens 326 ->
+// 312, 2048 tokens 616 -> 624; d = 512 (one): 1024 tokens 42 -> 31, 2048 tokens 57 -> 52, 4096
+// tokens 94.5 -> 94.7.
+constexpr int64_t kAccDeepMaxRows = 4096;
+
+template <bool BF16, int CPL>
+void launch_acc(dim3 grid, hipStream_t st, const AccArgs& a, bool deep) {
+  if constexpr (CPL <= 4) {
+    if (deep && a.nchunks == a.splits * CPL * kWave) {
+      hipLaunchKernelGGL((accumulate_kernel<CPL, BF16, 4, true>), grid, dim3(256), 0, st, a);
+      return;
+    }
+    if (deep) {
+      hipLaunchKernelGGL((accumulate_kernel<CPL, BF16, 4, false>), grid, dim3(256), 0, st, a);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((accumulate_kernel<CPL, BF16, 0, false>), grid, dim3(256), 0, st, a);
+}
+
 template <bool BF16>
-hipError_t dispatch_acc(int cpl, dim3 grid, hipStream_t st, const AccArgs& a) {
+hipError_t dispatch_acc(int cpl, dim3 grid, hipStream_t st, const AccArgs& a, bool deep) {
   switch (cpl) {
-    case 1: hipLaunchKernelGGL((accumulate_kernel<1, BF16>), grid, dim3(256), 0, st, a); break;
-    case 2: hipLaunchKernelGGL((accumulate_kernel<2, BF16>), grid, dim3(256), 0, st, a); break;
-    case 4: hipLaunchKernelGGL((accumulate_kernel<4, BF16>), grid, dim3(256), 0, st, a); break;
-    case 8: hipLaunchKernelGGL((accumulate_kernel<8, BF16>), grid, dim3(256), 0, st, a); break;
-    default: hipLaunchKernelGGL((accumulate_kernel<16, BF16>), grid, dim3(256), 0, st, a); break;
+    case 1: launch_acc<BF16, 1>(grid, st, a, deep); break;
+    case 2: launch_acc<BF16, 2>(grid, st, a, deep); break;
+    case 4: launch_acc<BF16, 4>(grid, st, a, deep); break;
+    case 8: launch_acc<BF16, 8>(grid, st, a, deep); break;
+    default: launch_acc<BF16, 16>(grid, st, a, deep); break;
   }
   return hipGetLastError();
 }
@@ -931,8 +958,9 @@ hipError_t launch_accumulate(const Shape& s, const void* v, const int32_t* idx, 
   }
   int64_t blocks = (s.T * splits + 3) / 4;
   if (blocks > 16384) blocks = 16384;
-  return s.bf16 ? dispatch_acc<true>(cpl, dim3((unsigned)blocks), st, a)
-                : dispatch_acc<false>(cpl, dim3((unsigned)blocks), st, a);
+  const bool deep = s.T * rows64 <= kAccDeepMaxRows;
+  return s.bf16 ? dispatch_acc<true>(cpl, dim3((unsigned)blocks), st, a, deep)
+                : dispatch_acc<false>(cpl, dim3((unsigned)blocks), st, a, deep);
 }
 
 hipError_t launch_token_centric(const Shape& s, const void* x, const void* u, const void* v,
