@@ -5,11 +5,11 @@
 //   dx_t = sum over t's slots of dh_p u_e,
 //   du_e = sum over e's tasks of dh_p x_t,  dv_e = sum over e's tasks of a_p dy_t,
 //   dscores_p = g_p (dgates_p - sum over the (t, h) row of g dgates)   (softmax, Eq. 2).
-// token pass: one wavefront per token gathers each slot's u and v rows (as the token-centric
-//   forward does), forms h, da, a, dh, dgates and sums dx in slot order;
-// expert pass: one wavefront per active expert walks its segment of the schedule (task ids
-//   ascending) and sums du and dv in that order: the expert-major order makes the per-expert
-//   gradients plain sequential sums, with no atomics, so every run gives the same bits;
+// expert pass: one wavefront walks the segments of one or two active experts (task ids
+//   ascending), forms h, da, a, dh and dgates of every task and sums du and dv in that order: the
+//   expert-major order makes the per-expert gradients plain sequential sums, with no atomics, so
+//   every run gives the same bits;
+// dx: the forward's token-major routed sum with dh in the place of a and u in the place of v;
 // score pass: one wavefront per (token, head) row.
 // Router backward (selections fixed; S_p = s_r[i_p] + s_c[j_p]): tasks are sorted by sub-key
 // row (h, i) with the schedule's radix sort, and one wavefront per selected sub-key sums
@@ -38,7 +38,6 @@ struct BwdArgs {
   float* dv;
   float* dgates;
   float* dscores;
-  float* a;    // a_p per task (workspace)
   float* dh;   // dh_p per task (workspace)
   int64_t T;
   int64_t N;
@@ -48,7 +47,7 @@ struct BwdArgs {
   int hk;
   int K;
   int act;
-  int nchunks;  // 16-byte chunks of a stored row
+  int run;      // consecutive active experts per wave (at most 63)
 };
 
 __device__ __forceinline__ int clamp_id(int v, int64_t n) {
@@ -67,208 +66,193 @@ __device__ __forceinline__ float chunk_elem(const uint4& c, int k) {
   }
 }
 
-// Slots s0 .. s0 + GG - 1 of token t (expert e and gate g of slot s0 + i on lane i of ev/gv, an
-// offset of the slot batch sb): their u and v rows are loaded together, then h, da, a, dh and
-// dgates are formed and dx += dh u_e summed in slot order.
-template <int GG, int CPL, bool BF16>
-__device__ __forceinline__ void token_slots(const BwdArgs& a, int64_t t, int s0, int sb, int ev,
-                                            float gv, const uint4 (&xr)[CPL],
-                                            const float (&dyr)[CPL][BF16 ? 8 : 4],
-                                            const bool (&cv)[CPL],
-                                            float (&acc)[CPL][BF16 ? 8 : 4]) {
-  constexpr int EPC = BF16 ? 8 : 4;
-  const int l = lane_id();
-  const uint4* U = (const uint4*)a.u;
-  const uint4* V = (const uint4*)a.v;
-  const int64_t rc = a.nchunks;
-  uint4 ur[GG][CPL], vr[GG][CPL];
-#pragma unroll
-  for (int i = 0; i < GG; ++i) {
-    const int e = clamp_id(readlane_i32(ev, s0 + i - sb), a.N);
-#pragma unroll
-    for (int q = 0; q < CPL; ++q) {
-      ur[i][q] = cv[q] ? U[(int64_t)e * rc + l + kWave * q] : make_uint4(0, 0, 0, 0);
-      vr[i][q] = cv[q] ? V[(int64_t)e * rc + l + kWave * q] : make_uint4(0, 0, 0, 0);
-    }
-  }
-  // every row of the group is requested before the first product
-  __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-  for (int i = 0; i < GG; ++i) {
-    const int64_t p = t * a.hk + s0 + i;
-    const float g = readlane_f32(gv, s0 + i - sb);
-    float hs = 0.0f, ds = 0.0f;
-#pragma unroll
-    for (int q = 0; q < CPL; ++q)
-#pragma unroll
-      for (int k = 0; k < EPC; ++k) {
-        hs = fmaf(chunk_elem<BF16>(xr[q], k), chunk_elem<BF16>(ur[i][q], k), hs);
-        ds = fmaf(dyr[q][k], chunk_elem<BF16>(vr[i][q], k), ds);
-      }
-    const float h = wave_sum_uniform(hs);
-    const float da = wave_sum_uniform(ds);
-    const float act = activation(a.act, h);
-    const float dh = da * g * activation_grad(a.act, h);
-    if (l == 0) {
-      a.a[p] = g * act;
-      a.dh[p] = dh;
-      a.dgates[p] = da * act;
-    }
-#pragma unroll
-    for (int q = 0; q < CPL; ++q)
-#pragma unroll
-      for (int k = 0; k < EPC; ++k) acc[q][k] = fmaf(dh, chunk_elem<BF16>(ur[i][q], k), acc[q][k]);
-  }
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+
+// A 64-position window of the schedule: lane l holds the task, expert and gate of position
+// base + l (positions from end on repeat the last one).
+struct TaskWindow {
+  int64_t base;
+  int p;
+  int e;
+  float g;
+};
+
+__device__ __forceinline__ void load_window(const BwdArgs& a, int64_t base, int64_t end,
+                                            TaskWindow& w) {
+  const int64_t pos = base + lane_id();
+  w.base = base;
+  w.p = clamp_id(a.perm[pos < end ? pos : end - 1], a.M);
+  w.e = clamp_id(a.idx[w.p], a.N);
+  w.g = a.gates[w.p];
 }
 
-// Token pass: one wave per token. The token's experts and gates are read 64 slots at a time
-// (one load per lane), and the slots then go through G at a time with all of their u and v
-// rows in flight, whole groups first and the rest singly, so that no row load waits behind the
-// previous slot's work. FULL: the row is exactly CPL * 64 chunks (no load carries a guard).
-template <int CPL, bool BF16, bool FULL>
-__global__ __launch_bounds__(256) void bwd_token_kernel(BwdArgs a) {
-  constexpr int EPC = BF16 ? 8 : 4;
-  constexpr int G = CPL >= 8 ? 1 : (CPL >= 4 ? 2 : 4);
-  const int l = lane_id();
-  const uint4* X = (const uint4*)a.x;
-  const int64_t rc = a.nchunks;
-  bool cv[CPL];
-#pragma unroll
-  for (int q = 0; q < CPL; ++q) cv[q] = FULL || (l + kWave * q) < a.nchunks;
-  const int64_t stride = (int64_t)gridDim.x * 4;
-  for (int64_t t = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); t < a.T; t += stride) {
-    uint4 xr[CPL];
-    float dyr[CPL][EPC];
-    float acc[CPL][EPC];
-#pragma unroll
-    for (int q = 0; q < CPL; ++q) {
-      const int c = l + kWave * q;
-      xr[q] = cv[q] ? X[t * rc + c] : make_uint4(0, 0, 0, 0);
-      const float4* dyc = (const float4*)(a.dy + t * a.d + (int64_t)c * EPC);
-#pragma unroll
-      for (int k = 0; k < EPC; k += 4) {
-        const float4 y4 = cv[q] ? dyc[k / 4] : make_float4(0.f, 0.f, 0.f, 0.f);
-        dyr[q][k] = y4.x;
-        dyr[q][k + 1] = y4.y;
-        dyr[q][k + 2] = y4.z;
-        dyr[q][k + 3] = y4.w;
-      }
-#pragma unroll
-      for (int k = 0; k < EPC; ++k) acc[q][k] = 0.0f;
-    }
-    for (int sb = 0; sb < a.hk; sb += kWave) {
-      const int n = a.hk - sb < kWave ? a.hk - sb : kWave;
-      const int64_t pl = t * a.hk + sb + (l < n ? l : n - 1);
-      const int ev = a.idx[pl];
-      const float gv = a.gates[pl];
-      int s0 = sb;
-      for (; s0 + G <= sb + n; s0 += G)
-        token_slots<G, CPL, BF16>(a, t, s0, sb, ev, gv, xr, dyr, cv, acc);
-      for (; s0 < sb + n; ++s0) token_slots<1, CPL, BF16>(a, t, s0, sb, ev, gv, xr, dyr, cv, acc);
-    }
-#pragma unroll
-    for (int q = 0; q < CPL; ++q) {
-      if (!cv[q]) continue;
-      const int c = l + kWave * q;
-      float4* o = (float4*)(a.dx + t * a.d + (int64_t)c * EPC);
-#pragma unroll
-      for (int k = 0; k < EPC; k += 4) o[k / 4] = make_float4(acc[q][k], acc[q][k + 1], acc[q][k + 2], acc[q][k + 3]);
-    }
+// Four elements of a stored row: 8 bytes of bf16 or 16 bytes of fp32.
+template <bool BF16>
+struct Quad;
+template <>
+struct Quad<true> {
+  typedef unsigned int raw __attribute__((ext_vector_type(2)));
+  static __device__ __forceinline__ float at(const raw& v, int k) {
+    const uint32_t w = k < 2 ? v.x : v.y;
+    return (k & 1) ? bf16_hi(w) : bf16_lo(w);
   }
-}
+  static __device__ __forceinline__ float dot(const raw& p, const raw& q, float acc) {
+    return dot2_bf16(p.y, q.y, dot2_bf16(p.x, q.x, acc));
+  }
+};
+template <>
+struct Quad<false> {
+  typedef f32x4_t raw;
+  static __device__ __forceinline__ float at(const raw& v, int k) { return v[k]; }
+  static __device__ __forceinline__ float dot(const raw& p, const raw& q, float acc) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) acc = fmaf(p[k], q[k], acc);
+    return acc;
+  }
+};
 
-// Tasks j0 .. j0 + GG - 1 of the lanes' batch (slot pl, a_p apl, dh_p dhl on lane j): all their
-// token and dy rows are loaded, then du += dh_p x_t and dv += a_p dy_t in task order.
-template <int GG, int CPL, bool BF16>
-__device__ __forceinline__ void task_group(const BwdArgs& a, const uint4* X, int64_t rc,
-                                           const bool (&cv)[CPL], int pl, float apl, float dhl,
-                                           int j0, float (&du)[CPL][BF16 ? 8 : 4],
-                                           float (&dv)[CPL][BF16 ? 8 : 4]) {
-  constexpr int EPC = BF16 ? 8 : 4;
-  const int l = lane_id();
-  uint4 xr[GG][CPL];
-  float4 yr[GG][CPL][EPC / 4];
-#pragma unroll
-  for (int i = 0; i < GG; ++i) {
-    const int64_t t = readlane_i32(pl, j0 + i) / a.hk;
-#pragma unroll
-    for (int q = 0; q < CPL; ++q) {
-      const int c = l + kWave * q;
-      xr[i][q] = cv[q] ? X[t * rc + c] : make_uint4(0, 0, 0, 0);
-      const float4* dyc = (const float4*)(a.dy + t * a.d + (int64_t)c * EPC);
-#pragma unroll
-      for (int k = 0; k < EPC / 4; ++k) yr[i][q][k] = cv[q] ? dyc[k] : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-  }
-  // every load above is issued before the first product (left alone, the scheduler interleaves
-  // them with the products and waits for each row in turn)
-  __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-  for (int i = 0; i < GG; ++i) {
-    const float ap = readlane_f32(apl, j0 + i), dhp = readlane_f32(dhl, j0 + i);
-#pragma unroll
-    for (int q = 0; q < CPL; ++q) {
-#pragma unroll
-      for (int k = 0; k < EPC; k += 4) {
-        const float4 yv = yr[i][q][k / 4];
-        dv[q][k] = fmaf(ap, yv.x, dv[q][k]);
-        dv[q][k + 1] = fmaf(ap, yv.y, dv[q][k + 1]);
-        dv[q][k + 2] = fmaf(ap, yv.z, dv[q][k + 2]);
-        dv[q][k + 3] = fmaf(ap, yv.w, dv[q][k + 3]);
-      }
-#pragma unroll
-      for (int k = 0; k < EPC; ++k) du[q][k] = fmaf(dhp, chunk_elem<BF16>(xr[i][q], k), du[q][k]);
-    }
-  }
-}
-
-// Expert pass. The segment's tasks are taken 64 at a time: lane j loads the j-th one's slot,
-// a and dh (one round trip for all of them), and the tasks then go through in order, G at a time
-// with all of their token and dy rows in flight before the first product (the sums keep task
-// order, so du and dv are the same as with one task at a time). FULL: the row is exactly CPL * 64
-// chunks and no load carries a guard (guarded loads made the compiler wait for each chunk).
-template <int CPL, bool BF16, bool FULL>
+// Expert pass: a wave takes a.run consecutive active experts. It reads the run's segment bounds
+// and then the segments' tasks, experts and gates 64 positions at a time with one load per lane.
+// Per expert it loads u_e and v_e once and takes the tasks G at a time with all of their token and
+// dy rows in flight: the dot products h = x . u and da = dy . v, one activation for the group (lane
+// i finishes task i), then du += dh x and dv += a dy in task order.
+//
+// Bound by memory: at the training shape u, v and the fp32 rows du and dv are 22 GB once (4.7 ms
+// at the rate of a large copy), the token and dy rows 26 GB from the caches. Forming the dots here
+// and not in a token pass of their own saves that pass's v gather and its second read of x and dy; its
+// dx = sum of dh u stays token-major (launch_accumulate with dh and u). Each XCD takes a contiguous
+// share of the active experts, so that a token's experts in one grid row find its rows in that XCD's
+// L2; du and dv leave with non-temporal stores, and u and v are read with the non-temporal hint when
+// the tables do not stay in the MALL (NTL), so that neither pushes those rows out. A lane holds four
+// neighbouring elements of every 256: fp32 rows move in whole lines (with the eight elements of a
+// 16-byte bf16 load every store would write half lines, and the non-temporal stores cost 1.5 ms
+// instead of saving 0.6). Measured at the training shape, token pass and expert pass 8.73 ms before, this pass
+// and the routed sum 7.02 ms (two experts per wave; four 7.03, eight 7.32; two tasks in flight instead of
+// one 7.49; four waves sharing an expert's columns 7.27); 4093 tokens, 2^16 experts of d = 512: 236 ->
+// 156 us (G = 4; 161 with two in flight, 169 with six).
+template <int CPL, bool BF16, bool FULL, int G, bool NTL>
 __global__ __launch_bounds__(256) void bwd_expert_kernel(BwdArgs a) {
-  constexpr int EPC = BF16 ? 8 : 4;
-  constexpr int G = CPL >= 8 ? 1 : 2;
+  typedef Quad<BF16> Q;
+  typedef typename Q::raw raw;
   const int l = lane_id();
-  const uint4* X = (const uint4*)a.x;
-  const int64_t rc = a.nchunks;
+  const int64_t rc = a.d / 4;
   bool cv[CPL];
 #pragma unroll
-  for (int q = 0; q < CPL; ++q) cv[q] = FULL || (l + kWave * q) < a.nchunks;
+  for (int q = 0; q < CPL; ++q) cv[q] = FULL || (l + kWave * q) < rc;
   const int64_t na = *a.n_active < a.cap ? *a.n_active : a.cap;
-  const int64_t stride = (int64_t)gridDim.x * 4;
-  for (int64_t r = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); r < na; r += stride) {
-    float du[CPL][EPC], dv[CPL][EPC];
+  // the grid covers a.cap experts; the workgroups that the active ones need are shared out to the
+  // XCDs (workgroup b runs on XCD b % 8) in contiguous parts
+  const int64_t nblk = (na + 4 * a.run - 1) / (4 * a.run);
+  if (blockIdx.x >= nblk) return;
+  const int64_t per_xcd = nblk / 8, extra = nblk % 8, xcd = blockIdx.x % 8;
+  const int64_t blk = xcd * per_xcd + (xcd < extra ? xcd : extra) + blockIdx.x / 8;
+  const int64_t r0 = (blk * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * a.run;
+  if (r0 >= na) return;
+  const int n = (int)(na - r0 < a.run ? na - r0 : a.run);
+  int off = a.offsets[r0 + (l < n ? l : n)];
+  off = off < 0 ? 0 : (off > a.M ? (int)a.M : off);
+  const int hk_shift = (a.hk & (a.hk - 1)) == 0 ? __builtin_ctz((unsigned)a.hk) : -1;
+  auto token_of = [&](int p) { return hk_shift >= 0 ? p >> hk_shift : p / a.hk; };
+  const int last = readlane_i32(off, n);  // end of the wave's positions
+  TaskWindow w;
+  w.base = -1;
+  for (int i = 0; i < n; ++i) {
+    const int b = readlane_i32(off, i), e = readlane_i32(off, i + 1);
+    f32x4_t du[CPL], dv[CPL];
 #pragma unroll
-    for (int q = 0; q < CPL; ++q)
+    for (int q = 0; q < CPL; ++q) du[q] = dv[q] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    raw ur[CPL], vr[CPL];
+    for (int64_t pos = b; pos < e;) {
+      if (w.base < 0 || pos < w.base || pos >= w.base + kWave)
+        load_window(a, pos, last > pos ? last : pos + 1, w);
+      const int j0 = (int)(pos - w.base);
+      int cnt = (int)(e - pos < G ? e - pos : G);
+      if (cnt > kWave - j0) cnt = kWave - j0;
+      if (pos == b) {
+        const int64_t row = (int64_t)readlane_i32(w.e, j0) * rc + l;
+        const raw* U = (const raw*)a.u + row;
+        const raw* V = (const raw*)a.v + row;
 #pragma unroll
-      for (int k = 0; k < EPC; ++k) du[q][k] = dv[q][k] = 0.0f;
-    int64_t b = a.offsets[r], e = a.offsets[r + 1];
-    b = b < 0 ? 0 : (b > a.M ? a.M : b);
-    e = e < b ? b : (e > a.M ? a.M : e);
-    for (int64_t base = b; base < e; base += kWave) {
-      const int n = (int)(e - base < kWave ? e - base : kWave);
-      const int pl = clamp_id(a.perm[base + (l < n ? l : n - 1)], a.M);
-      const float apl = a.a[pl], dhl = a.dh[pl];
-      // whole groups of G tasks, then the remaining ones singly: every product of a group is
-      // unconditional, so the compiler cannot move a task's loads behind the previous task's work
-      int j0 = 0;
-      for (; j0 + G <= n; j0 += G) task_group<G, CPL, BF16>(a, X, rc, cv, pl, apl, dhl, j0, du, dv);
-      for (; j0 < n; ++j0) task_group<1, CPL, BF16>(a, X, rc, cv, pl, apl, dhl, j0, du, dv);
+        for (int q = 0; q < CPL; ++q) {
+          ur[q] = vr[q] = raw{};
+          if (cv[q]) {
+            ur[q] = NTL ? __builtin_nontemporal_load(U + kWave * q) : U[kWave * q];
+            vr[q] = NTL ? __builtin_nontemporal_load(V + kWave * q) : V[kWave * q];
+          }
+        }
+      }
+      raw xr[G][CPL];
+      f32x4_t yr[G][CPL];
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        // past the group's last task its rows are loaded again (and not added)
+        const int64_t t = token_of(readlane_i32(w.p, j0 + (g < cnt ? g : cnt - 1)));
+        const raw* X = (const raw*)a.x + t * rc + l;
+        const f32x4_t* Y = (const f32x4_t*)a.dy + t * rc + l;
+#pragma unroll
+        for (int q = 0; q < CPL; ++q) {
+          xr[g][q] = raw{};
+          yr[g][q] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+          if (cv[q]) {
+            xr[g][q] = X[kWave * q];
+            yr[g][q] = Y[kWave * q];
+          }
+        }
+      }
+      // every load above is issued before the first product (left alone, the scheduler interleaves
+      // them with the products and waits for each row in turn)
+      __builtin_amdgcn_sched_barrier(0);
+      float hv = 0.0f, dav = 0.0f, gv = 0.0f;
+      int pv = 0;
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        float hs = 0.0f, ds = 0.0f;
+#pragma unroll
+        for (int q = 0; q < CPL; ++q) {
+          hs = Q::dot(ur[q], xr[g][q], hs);
+#pragma unroll
+          for (int k = 0; k < 4; ++k) ds = fmaf(yr[g][q][k], Q::at(vr[q], k), ds);
+        }
+        if (g < cnt) {
+          const float h = wave_sum_uniform(hs), da = wave_sum_uniform(ds);
+          const float gt = readlane_f32(w.g, j0 + g);
+          const int p = readlane_i32(w.p, j0 + g);
+          if (l == g) {
+            hv = h;
+            dav = da;
+            gv = gt;
+            pv = p;
+          }
+        }
+      }
+      const float act = activation(a.act, hv);
+      const float av = gv * act, dhv = dav * gv * activation_grad(a.act, hv);
+      if (l < cnt) {
+        a.dh[pv] = dhv;
+        a.dgates[pv] = dav * act;
+      }
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        if (g < cnt) {
+          const float ap = readlane_f32(av, g), dhp = readlane_f32(dhv, g);
+#pragma unroll
+          for (int q = 0; q < CPL; ++q)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+              dv[q][k] = fmaf(ap, yr[g][q][k], dv[q][k]);
+              du[q][k] = fmaf(dhp, Q::at(xr[g][q], k), du[q][k]);
+            }
+        }
+      }
+      pos += cnt;
     }
+    f32x4_t* ou = (f32x4_t*)a.du + (r0 + i) * rc + l;
+    f32x4_t* ov = (f32x4_t*)a.dv + (r0 + i) * rc + l;
 #pragma unroll
     for (int q = 0; q < CPL; ++q) {
       if (!cv[q]) continue;
-      const int c = l + kWave * q;
-      float4* ou = (float4*)(a.du + r * a.d + (int64_t)c * EPC);
-      float4* ov = (float4*)(a.dv + r * a.d + (int64_t)c * EPC);
-#pragma unroll
-      for (int k = 0; k < EPC; k += 4) {
-        ou[k / 4] = make_float4(du[q][k], du[q][k + 1], du[q][k + 2], du[q][k + 3]);
-        ov[k / 4] = make_float4(dv[q][k], dv[q][k + 1], dv[q][k + 2], dv[q][k + 3]);
-      }
+      __builtin_nontemporal_store(du[q], ou + kWave * q);
+      __builtin_nontemporal_store(dv[q], ov + kWave * q);
     }
   }
 }
@@ -536,39 +520,40 @@ int cpl_of(int nchunks) {
   return c;
 }
 
-template <bool BF16>
-hipError_t dispatch_bwd(int cpl, int64_t t_blocks, int64_t e_blocks, hipStream_t st,
-                        const BwdArgs& a) {
-#define OMNIMOE_BWD(C)                                                                    \
-  case C:                                                                                 \
-    if (a.nchunks == C * kWave)                                                           \
-      hipLaunchKernelGGL((bwd_token_kernel<C, BF16, true>), dim3((unsigned)t_blocks),       \
-                         dim3(256), 0, st, a);                                            \
-    else                                                                                  \
-      hipLaunchKernelGGL((bwd_token_kernel<C, BF16, false>), dim3((unsigned)t_blocks),      \
-                         dim3(256), 0, st, a);                                            \
-    if (a.nchunks == C * kWave)                                                           \
-      hipLaunchKernelGGL((bwd_expert_kernel<C, BF16, true>), dim3((unsigned)e_blocks),      \
-                         dim3(256), 0, st, a);                                            \
-    else                                                                                  \
-      hipLaunchKernelGGL((bwd_expert_kernel<C, BF16, false>), dim3((unsigned)e_blocks),     \
-                         dim3(256), 0, st, a);                                            \
-    break;
-  switch (cpl) {
-    OMNIMOE_BWD(1)
-    OMNIMOE_BWD(2)
-    OMNIMOE_BWD(4)
-    OMNIMOE_BWD(8)
-    default:
-      return hipErrorInvalidValue;
-  }
+// Tables up to this size stay in the MALL (256 MB) between the passes that read them.
+constexpr int64_t kMallTableBytes = 128ll << 20;
+
+template <bool BF16, int CPL, int G>
+void launch_bwd(hipStream_t st, const BwdArgs& a) {
+  const dim3 grid((unsigned)((a.cap + 4 * a.run - 1) / (4 * a.run)));
+  const bool full = a.d == CPL * 4 * kWave;
+  const bool ntl = a.N * (int64_t)a.d * (BF16 ? 2 : 4) > kMallTableBytes;
+#define OMNIMOE_BWD(F_, N_) \
+  hipLaunchKernelGGL((bwd_expert_kernel<CPL, BF16, F_, G, N_>), grid, dim3(256), 0, st, a)
+  if (full && ntl) OMNIMOE_BWD(true, true);
+  else if (full) OMNIMOE_BWD(true, false);
+  else if (ntl) OMNIMOE_BWD(false, true);
+  else OMNIMOE_BWD(false, false);
 #undef OMNIMOE_BWD
+}
+
+// cpl: 256-element pieces of a row, rounded up to a power of two (at most 16: d <= 4096).
+template <bool BF16>
+hipError_t dispatch_bwd(int cpl, hipStream_t st, const BwdArgs& a) {
+  switch (cpl) {
+    case 1: launch_bwd<BF16, 1, 4>(st, a); break;
+    case 2: launch_bwd<BF16, 2, 4>(st, a); break;
+    case 4: launch_bwd<BF16, 4, 2>(st, a); break;
+    case 8: launch_bwd<BF16, 8, 1>(st, a); break;
+    case 16: launch_bwd<BF16, 16, 1>(st, a); break;
+    default: return hipErrorInvalidValue;
+  }
   return hipGetLastError();
 }
 
 }  // namespace
 
-size_t backward_ws_bytes(int64_t M) { return 2 * (((size_t)M * 4 + 255) & ~(size_t)255); }
+size_t backward_ws_bytes(int64_t M) { return ((size_t)M * 4 + 255) & ~(size_t)255; }
 
 hipError_t launch_expert_backward(const Shape& s, const void* x, const void* u, const void* v,
                                   const int32_t* idx, const float* gates, const int32_t* perm,
@@ -591,8 +576,7 @@ hipError_t launch_expert_backward(const Shape& s, const void* x, const void* u, 
   a.dv = dv;
   a.dgates = dgates;
   a.dscores = dscores;
-  a.a = (float*)ws;
-  a.dh = (float*)((char*)ws + (((size_t)s.M * 4 + 255) & ~(size_t)255));
+  a.dh = (float*)ws;
   a.T = s.T;
   a.N = s.N;
   a.M = s.M;
@@ -601,14 +585,13 @@ hipError_t launch_expert_backward(const Shape& s, const void* x, const void* u, 
   a.hk = s.hk;
   a.K = s.K;
   a.act = s.act;
-  a.nchunks = s.bf16 ? s.d / 8 : s.d / 4;
-  const int cpl = cpl_of(a.nchunks);
-  int64_t tb = (s.T + 3) / 4;
-  if (tb > 16384) tb = 16384;
-  int64_t eb = (a.cap + 3) / 4;
-  if (eb > 65536) eb = 65536;
-  hipError_t e = s.bf16 ? dispatch_bwd<true>(cpl, tb, eb, st, a)
-                        : dispatch_bwd<false>(cpl, tb, eb, st, a);
+  // Two experts per wave share its window loads (training shape 7.08 -> 7.02 ms); one below 32768,
+  // where halving the waves costs more (10^4 experts of d = 256: 83 us with one, 92 with two).
+  a.run = a.cap >= 32768 ? 2 : 1;
+  hipError_t e = s.bf16 ? dispatch_bwd<true>(cpl_of(s.d / 4), st, a)
+                        : dispatch_bwd<false>(cpl_of(s.d / 4), st, a);
+  // dx_t = sum of dh_p u_e over t's slots: the token-major routed sum with dh and u
+  if (e == hipSuccess) e = launch_accumulate(s, u, idx, a.dh, dx, st);
   if (e != hipSuccess) return e;
   int64_t sb = (s.rows + 3) / 4;
   if (sb > 16384) sb = 16384;

@@ -7,7 +7,7 @@ import pytest
 
 import oracle
 import synth
-from gpu_support import grouped_gap_bound, to_dev, upload
+from gpu_support import backward_error_bounds, grouped_gap_bound, to_dev, upload
 
 pytestmark = pytest.mark.gpu
 
@@ -60,3 +60,49 @@ def test_routed_sum_rows_in_flight(case):
     assert np.all(gap <= grouped_gap_bound(f, idx, g, d, dsc.act))
     # every form sums a token's slots one after another, so the bits agree
     assert np.array_equal(y.cpu().numpy().view(np.uint8), y_tc.cpu().numpy().view(np.uint8))
+
+
+# (T, d, n_rows, n_cols, H, K, dtype): row pieces of 256 elements, whole and partial, one to sixteen per lane; segments longer
+# than the 64 positions of a wave's window and of every remainder; one and two experts per wave (from 32768 rows on).
+BWD_CASES = [(300, 200, 2, 3, 1, 4, "bf16"), (131, 256, 3, 4, 2, 5, "bf16"), (90, 512, 5, 7, 1, 3, "bf16"),
+             (77, 1024, 6, 6, 2, 3, "bf16"), (40, 1032, 4, 9, 1, 7, "bf16"), (67, 2048, 5, 8, 1, 6, "bf16"),
+             (33, 4096, 4, 4, 1, 5, "bf16"), (150, 264, 3, 3, 1, 2, "f32"), (50, 2048, 5, 5, 2, 3, "f32"),
+             (700, 64, 190, 190, 4, 13, "bf16")]
+
+
+@pytest.mark.parametrize("case", BWD_CASES, ids=[str(c) for c in BWD_CASES])
+def test_expert_backward_segments(case):
+    T, d, nr, nc, H, K, dtype = case
+    say(f"[expert backward] {case}")
+    w = synth.Workload("bwd", T=T, d=d, n_rows=nr, n_cols=nc, d_key=8, H=H, K=K, dtype=dtype)
+    inp = synth.make_inputs(w)
+    f = {k: synth.as_f32(v) for k, v in inp.items()}
+    if w.N <= 4096:
+        idx, g = _random_routing(w)
+    else:
+        rng = np.random.default_rng(5)
+        idx = np.stack([rng.choice(w.N, K, replace=False) for _ in range(T * H)]).reshape(T, H, K).astype(np.int32)
+        g = rng.random((T, H, K)).astype(np.float32)
+    dsc = oracle.desc(w)
+    perm, act, off, _ = oracle.schedule(dsc, idx)
+    dy = np.random.default_rng(11).standard_normal((T, d)).astype(np.float32)
+    ref = oracle.expert_backward(dsc, f["x"], f["u"], f["v"], idx, g.astype(np.float64), dy.astype(np.float64))
+    bnd = backward_error_bounds(f["x"], f["u"], f["v"], idx, g, dy, np.vectorize(lambda z: oracle.act(0, z)),
+                                np.vectorize(lambda z: oracle.act_grad(0, z)))
+    A, n = min(w.M, w.N), len(act)
+    out = {k: torch.full(shape, float("nan"), device="cuda") for k, shape in
+           [("dx", (T, d)), ("du", (A, d)), ("dv", (A, d)), ("dgates", (T, H, K)), ("dscores", (T, H, K))]}
+    offd = torch.full((A + 1,), -1, dtype=torch.int32, device="cuda")
+    offd[:n + 1] = to_dev(off)
+    dev = upload(inp)
+    P.omnimoe_expert_backward(B.make_desc(w), dev["x"], dev["u"], dev["v"], to_dev(idx), to_dev(g), to_dev(perm), offd,
+                              torch.tensor([n], dtype=torch.int32, device="cuda"), to_dev(dy), out["dx"], out["du"],
+                              out["dv"], out["dgates"], out["dscores"])
+    torch.cuda.synchronize()
+    for k, rk in (("dx", "dx"), ("du", "du_rows"), ("dv", "dv_rows"), ("dgates", "dgates"), ("dscores", "dscores")):
+        got = out[k].cpu().numpy()[:n if k in ("du", "dv") else None]
+        err = np.abs(got.astype(np.float64) - ref[rk])
+        say(f"  {k}: max err / bound {(err / (2 * bnd[k] + 1e-30)).max():.2f}")
+        assert np.all(err <= 2 * bnd[k] + 1e-30), k
+    # rows past the active experts are not written
+    assert torch.isnan(out["du"][n:]).all() and torch.isnan(out["dv"][n:]).all()
