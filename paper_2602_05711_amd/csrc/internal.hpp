@@ -109,6 +109,10 @@ hipError_t launch_group_schedule(const Shape& s, const int32_t* idx, int32_t* pe
                                  int32_t* active, int32_t* n_active, void* ws,
                                  const int32_t** group_keys, hipStream_t st);
 
+// In-place exclusive scan of n 32-bit counts; partial holds exclusive_scan_partials(n) words.
+int64_t exclusive_scan_partials(int64_t n);
+hipError_t launch_exclusive_scan(int32_t* counts, int64_t n, int32_t* partial, hipStream_t st);
+
 // a[p] = g_p * act(x_t . u_e) over the expert-major order given by perm (sorted_keys may be
 // NULL: the kernel then reads idx[perm[pos]]).
 hipError_t launch_expert_dot(const Shape& s, const void* x, const void* u, const int32_t* idx,

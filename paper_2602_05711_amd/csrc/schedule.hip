@@ -1310,6 +1310,12 @@ size_t schedule_ws_bytes(int64_t M, int64_t N) {
   return b;
 }
 
+int64_t exclusive_scan_partials(int64_t n) { return (n + kTile - 1) / kTile; }
+
+hipError_t launch_exclusive_scan(int32_t* counts, int64_t n, int32_t* partial, hipStream_t st) {
+  return device_scan(ArrayVal{counts, n}, EmitScan{counts, n}, n, partial, st);
+}
+
 int group_key_bits(const Shape& s) {
   const int64_t cap = std::min<int64_t>(s.M, s.N);
   const int gb = digit_bits_total((cap + s.B - 1) / s.B);

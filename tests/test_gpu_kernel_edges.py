@@ -106,3 +106,51 @@ def test_expert_backward_segments(case):
         assert np.all(err <= 2 * bnd[k] + 1e-30), k
     # rows past the active experts are not written
     assert torch.isnan(out["du"][n:]).all() and torch.isnan(out["dv"][n:]).all()
+
+
+# (T, d, d_key, n_rows, n_cols, H, K, query, dtype): blocks of 1, 2, 8 and 16 slots with partial ones, more than 64 picks per
+# token, a sub-key with hundreds of picks, tables of one row and of 4096; d_key pieces of 256 elements, whole and
+# partial, one to sixteen of them (combinations that eight divides and that it does not).
+ROUTE_BWD_CASES = [(1, 16, 8, 3, 4, 1, 5, "split", "bf16"), (70, 64, 24, 5, 6, 2, 1, "split", "bf16"),
+                   (300, 2048, 1024, 6, 9, 2, 13, "split", "bf16"), (90, 1544, 768, 8, 7, 1, 17, "split", "bf16"),
+                   (129, 264, 264, 12, 3, 3, 30, "shared", "bf16"), (33, 256, 64, 4096, 2, 1, 64, "split", "bf16"),
+                   (700, 128, 64, 1, 40, 5, 2, "split", "f32"), (50, 2048, 2048, 9, 9, 1, 8, "shared", "f32"),
+                   (17, 4096, 4096, 5, 5, 2, 20, "shared", "bf16"), (5000, 64, 32, 16, 16, 4, 16, "split", "bf16")]
+
+
+@pytest.mark.parametrize("case", ROUTE_BWD_CASES, ids=[str(c) for c in ROUTE_BWD_CASES])
+def test_route_backward_picks(case):
+    T, d, dk, nr, nc, H, K, query, dtype = case
+    say(f"[route backward] {case}")
+    w = synth.Workload("rbwd", T=T, d=d, n_rows=nr, n_cols=nc, d_key=dk, H=H, K=K, query_mode=query, dtype=dtype)
+    rng = np.random.default_rng(K + T)
+    idx = np.stack([rng.choice(w.N, K, replace=False) for _ in range(T * H)]).reshape(T, H, K).astype(np.int32)
+    kr, kc = synth.make_keys(w)
+    x = synth.make_x(w)
+    fx, fr, fc = synth.as_f32(x), synth.as_f32(kr), synth.as_f32(kc)
+    ds = rng.standard_normal((T, H, K)).astype(np.float32)
+    dx0 = rng.standard_normal((T, d)).astype(np.float32)
+    dsc = oracle.desc(w)
+    ref = oracle.route_backward(dsc, fx, fr, fc, idx, ds, dx=dx0)
+    absb = oracle.route_backward(dsc, np.abs(fx), np.abs(fr), np.abs(fc), idx, np.abs(ds), dx=np.abs(dx0))
+    outs = []
+    for _ in range(2):
+        dx = to_dev(dx0.copy())
+        dkr = torch.full((H, nr, dk), float("nan"), device="cuda")
+        dkc = torch.full((H, nc, dk), float("nan"), device="cuda")
+        P.omnimoe_route_backward(B.make_desc(w), to_dev(x), to_dev(kr), to_dev(kc), to_dev(idx), to_dev(ds), dx, dkr, dkc)
+        torch.cuda.synchronize()
+        outs.append([v.cpu().numpy() for v in (dx, dkr, dkc)])
+    # Every element is a fp32 sum of n terms (and of products): gamma_n times the sum of their absolute values (Higham),
+    # whatever the order, with two more roundings for the block sums of the weights and the products.
+    u = 2.0 ** -24
+    hd = np.arange(H)[None, :, None]
+    n_r = np.bincount((hd * nr + idx // nc).ravel(), minlength=H * nr).reshape(H, nr, 1) + 3
+    n_c = np.bincount((hd * nc + idx % nc).ravel(), minlength=H * nc).reshape(H, nc, 1) + 3
+    for k, got, rv, ab, n in zip(("dx", "dkeys_row", "dkeys_col"), outs[0], ref, absb, (2 * H * K + 3, n_r, n_c)):
+        bound = (n * u / (1 - n * u)) * ab + 1e-30
+        err = np.abs(got.astype(np.float64) - rv)
+        say(f"  {k}: max err / bound {(err / bound).max():.3f}")
+        assert np.all(err <= bound), k
+    for x0, x1 in zip(*outs):
+        assert np.array_equal(x0.view(np.uint8), x1.view(np.uint8))
