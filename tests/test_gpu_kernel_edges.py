@@ -7,7 +7,7 @@ import pytest
 
 import oracle
 import synth
-from gpu_support import backward_error_bounds, grouped_gap_bound, to_dev, upload
+from gpu_support import backward_error_bounds, grouped_gap_bound, higham_bound, to_dev, upload
 
 pytestmark = pytest.mark.gpu
 
@@ -154,3 +154,26 @@ def test_route_backward_picks(case):
         assert np.all(err <= bound), k
     for x0, x1 in zip(*outs):
         assert np.array_equal(x0.view(np.uint8), x1.view(np.uint8))
+
+
+# (T, d, d_key, n_rows, n_cols, H, query): fp32 logits on tiles of 64 x 64 with k steps of 32: one k step and several, whole and
+# partial, tokens and keys at a tile's edge and past it.
+F32_LOGIT_CASES = [(1, 16, 8, 1, 3, 1, "split"), (64, 64, 32, 32, 64, 2, "split"), (65, 80, 40, 64, 65, 1, "split"),
+                   (130, 264, 264, 21, 43, 3, "shared"), (63, 1024, 512, 63, 5, 1, "split")]
+
+
+@pytest.mark.parametrize("case", F32_LOGIT_CASES, ids=[str(c) for c in F32_LOGIT_CASES])
+def test_f32_logits(case):
+    T, d, dk, nr, nc, H, query = case
+    say(f"[fp32 logits] {case}")
+    w = synth.Workload("f32l", T=T, d=d, n_rows=nr, n_cols=nc, d_key=dk, H=H, K=1, query_mode=query, dtype="f32")
+    x, (kr, kc) = synth.make_x(w), synth.make_keys(w)
+    hs = torch.full((T, H, nr + nc), float("nan"), device="cuda")
+    idx = torch.empty((T, H, 1), dtype=torch.int32, device="cuda")
+    g = torch.empty((T, H, 1), device="cuda")
+    P.omnimoe_route(B.make_desc(w), to_dev(x), to_dev(kr), to_dev(kc), idx, g, half_scores=hs)
+    torch.cuda.synchronize()
+    c0 = dk if query == "split" else 0
+    for keys, xq, got in ((kr, x[:, :dk], hs[..., :nr]), (kc, x[:, c0:c0 + dk], hs[..., nr:])):
+        ref = np.einsum("tm,hjm->thj", xq.astype(np.float64), keys.astype(np.float64))
+        assert np.all(np.abs(got.cpu().numpy() - ref) <= higham_bound(xq, keys) + 1e-30)
