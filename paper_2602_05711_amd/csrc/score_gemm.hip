@@ -918,6 +918,11 @@ __global__ __launch_bounds__(256) void prefetch_kernel(PrefetchArgs a) {
 }
 
 constexpr int64_t kPrefetchMaxBytes = 128ll << 20;  // half the MALL
+// With few tiles per compute unit the operands are fetched about once, and the prefetch pass only adds
+// its own launch: layer call on the 2^20-expert tables with and without it, 300 tokens (128 tiles) 113.5
+// and 106.7 us, 1024 (256) 245 and 239, 3000 (768) 694 and 692, 4096 (1024) 890 and 893, 8192
+// (2048) 1876 and 1901, 16384 (4096) 3480 and 3561.
+constexpr int64_t kPrefetchMinTiles = 1024;
 
 hipError_t launch_score(const Shape& s, const void* x, const void* keys_row,
                         const void* keys_col, float* half_scores, hipStream_t st,
@@ -954,7 +959,9 @@ hipError_t launch_score(const Shape& s, const void* x, const void* keys_row,
     pa.n[1] = (int64_t)s.H * s.nr * s.dk * 2 / 16;
     pa.n[2] = (int64_t)s.H * s.nc * s.dk * 2 / 16;
     pa.sink = (uint32_t*)half_scores;
-    if ((pa.n[0] + pa.n[1] + pa.n[2]) * 16 <= kPrefetchMaxBytes)
+    const int64_t tiles = ((s.T + LM - 1) / LM) * (((int64_t)s.H * s.nr + LN - 1) / LN +
+                                                   ((int64_t)s.H * s.nc + LN - 1) / LN);
+    if (tiles >= kPrefetchMinTiles && (pa.n[0] + pa.n[1] + pa.n[2]) * 16 <= kPrefetchMaxBytes)
       hipLaunchKernelGGL(prefetch_kernel, dim3(4096), dim3(256), 0, st, pa);
   }
   if (s.bf16 && s.T >= 8 && s.T <= 64 && s.dk % 256 == 0 && s.dk <= 1024) {
