@@ -608,7 +608,7 @@ def main():
         if k in absent:
             kernels[k] = {"absent": absent[k], "ms": per[k]}
             continue
-        t_s = per[k] * 1e-3
+        t_s = max(per[k], 1e-6) * 1e-3  # a group that launches nothing takes no time
         if bound == "hbm":
             ach = amount / t_s / 1e9
             kernels[k] = {"bound": "hbm", "ms": per[k], "achieved": ach, "unit": "GB/s",

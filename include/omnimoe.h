@@ -306,10 +306,11 @@ omnimoe_status omnimoe_route_backward(const omnimoe_layer_desc* desc, const void
  * The expert compute is omnimoe_expert_forward's, or omnimoe_expert_forward_grouped's when
  * group_size > 1, dtype is bf16 and d % 64 == 0. With group_size 1, where the expert-major
  * order saves no memory traffic (at most 8192 tasks T*H*K, as in a decode step; at most one task
- * per two experts; or a u table N*d of at most 128 MiB, which stays in the GPU's last-level
- * cache), no schedule is formed: the same a_p are computed in slot order, with identical
- * results (by the selection kernel itself when there are at least 256 (token, head) rows;
- * omnimoe_layer_path tells which kernels run). With one head, K >= N / 64 and group_size 1,
+ * per two experts; a u table N*d of at most 128 MiB, which stays in the GPU's last-level
+ * cache, or of at most 256 MiB with at most six tasks per expert), no schedule is formed: the same
+ * a_p are computed in slot order, with identical results (by the selection kernel itself when there
+ * are at least 256 (token, head) rows, or, with enough tokens, in one kernel with the routed sum,
+ * whose time OMNIMOE_KERNEL_ACCUMULATE then holds; omnimoe_layer_path tells which kernels run). With one head, K >= N / 64 and group_size 1,
  * both products run dense over all experts (Eq. 14 with a single group): x . u for every
  * (token, expert) pair, gate and activation kept at the selected pairs (a_p rounded to bf16),
  * then y = A V; no schedule is formed. Workspace:

@@ -103,6 +103,9 @@ constexpr int64_t kSelectDotMinRows = 256;
 // Up to this many tasks the sort by expert is one launch, as cheap as the flag pass and scan
 // that replace it above (launch_group_schedule).
 constexpr int64_t kSortFreeMinTasks = 8192;
+// The slot-order dot and the routed sum in one kernel (not among the reported flags: like them it
+// forms no schedule).
+constexpr int32_t kPathTokenStage = 1 << 16;
 int32_t layer_path(const Shape& s) {
   const bool grouped = layer_grouped(s);
   const bool unscheduled = !grouped && omnimoe::slot_dot(s);
@@ -112,6 +115,9 @@ int32_t layer_path(const Shape& s) {
   if (unscheduled && s.rows >= kSelectDotMinRows && omnimoe::select_dot_fusable(s))
     f |= OMNIMOE_PATH_SELECT_DOT;
   if (omnimoe::dense_accumulate(s)) f |= OMNIMOE_PATH_DENSE_SUM;
+  if (unscheduled && !(f & (OMNIMOE_PATH_SELECT_DOT | OMNIMOE_PATH_DENSE_SUM)) &&
+      omnimoe::token_stage(s))
+    f |= kPathTokenStage;
   // Both products dense over all experts: no schedule and no per-task dot.
   if (omnimoe::dense_dot(s)) f = OMNIMOE_PATH_DENSE_SUM | OMNIMOE_PATH_DENSE_DOT;
   return f;
@@ -258,6 +264,13 @@ omnimoe_status layer_impl(const omnimoe_layer_desc* desc, const void* x, const v
     if (e) return hip_status(e);
   }
   mark(3);
+  if (path & kPathTokenStage) {
+    mark(4);
+    if ((e = omnimoe::launch_token_stage(s, x, u, v, idx, gates, y, strm))) return hip_status(e);
+    mark(5);
+    if (timer) ++timer->used;
+    return OMNIMOE_OK;
+  }
   if (unscheduled) {
     if (!fused && (e = omnimoe::launch_slot_dot(s, x, u, idx, gates, abuf, strm)))
       return hip_status(e);
@@ -636,7 +649,7 @@ omnimoe_status omnimoe_layer_path(const omnimoe_layer_desc* desc, int32_t* path)
   omnimoe_status st = check_desc(desc, &s);
   if (st) return st;
   if (!path) return OMNIMOE_ERR_INVALID_ARG;
-  *path = layer_path(s);
+  *path = layer_path(s) & ~kPathTokenStage;
   return OMNIMOE_OK;
 }
 

@@ -692,6 +692,143 @@ hipError_t dispatch_dot(int cpl, dim3 grid, hipStream_t st, const DotArgs& a) {
   return hipGetLastError();
 }
 
+// ---------------------------------------------------------------- the expert stage by tokens
+// One workgroup of four waves per token. The token's slots are taken up to 256 at a time: each wave
+// forms the a of a quarter of them (token row in registers, G u rows in flight, one activation for
+// all of the wave's slots, lane j finishing slot j) and leaves them in LDS; then each wave sums
+// a v over all of them, in slot order, for a quarter of the columns (eight v rows in flight).
+// Bound by the latency of its gathers (tables that stay in the MALL, one to a few workgroups per
+// compute unit): one launch and no a[] through memory instead of two, and the dots of a token share
+// its row in registers. Against slot_dot and accumulate (their stage, us): 256 tokens of 8 slots,
+// d = 64 fp32: 5.7 -> 2.5; 1000 tokens of 39 slots, d = 520 fp32: 34.7 -> 23.4; bf16, 64 slots, d = 1024:
+// 500 tokens 26.3 -> 22.0, 4000 tokens 157.6 -> 148.1; d = 512, 8000 tokens: 157 -> 137. With few
+// tokens of many slots the separate kernels have more waves (64 slots: 130 tokens 9.0 against 10.6,
+// 500 tokens 16.0 against 14.4; 128 slots: 250 tokens 25.0 against 28.1, 500 tokens 44.5 against 42.0;
+// 512 slots: 256 tokens 86 against 100, 512 tokens 182 against 150), hence token_stage's line at
+// 400 tokens, or six per slot. Rows of less than 64 chunks leave lanes of the quarter columns idle: from
+// 2048 tokens on one wave per token (token_centric_kernel) takes those (d = 200: 2000 tokens 30.8 and
+// 30.2, 8000 tokens 102 and 84).
+constexpr int64_t kTokenStageShortRows = 2048;  // tokens
+
+template <int CPL, bool BF16, bool FULL>
+__global__ __launch_bounds__(256) void token_stage_kernel(TokenArgs a) {
+  constexpr int EPC = BF16 ? 8 : 4;
+  constexpr int G = CPL >= 8 ? 1 : (CPL >= 4 ? 2 : (CPL >= 2 ? 4 : 8));
+  constexpr int CW = CPL >= 4 ? CPL / 4 : 1;  // chunks of a quarter row per lane
+  constexpr int GV = CW >= 4 ? 2 : (CW >= 2 ? 4 : 8);
+  constexpr int kBatch = 4 * kWave;
+  __shared__ float sa[kBatch];
+  __shared__ int se[kBatch];
+  const int l = lane_id(), w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint4* X = (const uint4*)a.x;
+  const uint4* U = (const uint4*)a.u;
+  const uint4* V = (const uint4*)a.v;
+  const int64_t rc = a.nchunks;
+  bool cv[CPL];
+#pragma unroll
+  for (int q = 0; q < CPL; ++q) cv[q] = FULL || (l + kWave * q) < a.nchunks;
+  // phase 2: wave w holds chunks w quarter + l + 64 q of the row
+  const int quarter = (a.nchunks + 3) / 4;
+  int c2[CW];
+  bool cv2[CW];
+#pragma unroll
+  for (int q = 0; q < CW; ++q) {
+    const int c = l + kWave * q;
+    cv2[q] = c < quarter && w * quarter + c < a.nchunks;
+    c2[q] = cv2[q] ? w * quarter + c : 0;
+  }
+  for (int64_t t = blockIdx.x; t < a.T; t += gridDim.x) {
+    uint4 xr[CPL];
+    load_row<CPL>(xr, X + t * rc, cv);
+    float acc[CW][EPC];
+#pragma unroll
+    for (int q = 0; q < CW; ++q)
+#pragma unroll
+      for (int k = 0; k < EPC; ++k) acc[q][k] = 0.0f;
+    for (int sb = 0; sb < a.hk; sb += kBatch) {
+      const int n = a.hk - sb < kBatch ? a.hk - sb : kBatch;
+      const int per = (n + 3) / 4;
+      const int lo = w * per < n ? w * per : n, cnt = lo + per < n ? per : n - lo;
+      if (cnt > 0) {
+        const int64_t p = t * a.hk + sb + lo + (l < cnt ? l : cnt - 1);
+        const int ev = clamp_i(a.idx[p], a.N);
+        const float gv = a.gates[p];
+        float hv = 0.0f;
+        for (int j = 0; j < cnt; j += G) {
+          uint4 ur[G][CPL];
+#pragma unroll
+          for (int i = 0; i < G; ++i)
+            load_row<CPL>(ur[i], U + (int64_t)readlane_i32(ev, j + i < cnt ? j + i : cnt - 1) * rc,
+                          cv);
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int i = 0; i < G; ++i) {
+            float h = 0.0f;
+#pragma unroll
+            for (int q = 0; q < CPL; ++q) h = chunk_dot<BF16>(ur[i][q], xr[q], h);
+            const float hs = wave_sum_uniform(h);
+            if (l == j + i) hv = hs;
+          }
+        }
+        if (l < cnt) {
+          sa[lo + l] = gv * activation(a.act, hv);
+          se[lo + l] = ev;
+        }
+      }
+      __syncthreads();
+      for (int j0 = 0; j0 < n; j0 += kWave) {
+        const int m = n - j0 < kWave ? n - j0 : kWave;
+        const int ev = se[j0 + (l < m ? l : m - 1)];
+        const float av = sa[j0 + (l < m ? l : m - 1)];
+        for (int j = 0; j < m; j += GV) {
+          uint4 vr[GV][CW];
+#pragma unroll
+          for (int i = 0; i < GV; ++i) {
+            const uint4* vb = V + (int64_t)readlane_i32(ev, j + i < m ? j + i : m - 1) * rc;
+#pragma unroll
+            for (int q = 0; q < CW; ++q) vr[i][q] = vb[c2[q]];
+          }
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int i = 0; i < GV; ++i) {
+            if (j + i < m) {
+              const float wgt = readlane_f32(av, j + i);
+#pragma unroll
+              for (int q = 0; q < CW; ++q) {
+                const uint4 c = vr[i][q];
+                if constexpr (BF16) {
+                  acc[q][0] = fmaf(wgt, bf16_lo(c.x), acc[q][0]);
+                  acc[q][1] = fmaf(wgt, bf16_hi(c.x), acc[q][1]);
+                  acc[q][2] = fmaf(wgt, bf16_lo(c.y), acc[q][2]);
+                  acc[q][3] = fmaf(wgt, bf16_hi(c.y), acc[q][3]);
+                  acc[q][4] = fmaf(wgt, bf16_lo(c.z), acc[q][4]);
+                  acc[q][5] = fmaf(wgt, bf16_hi(c.z), acc[q][5]);
+                  acc[q][6] = fmaf(wgt, bf16_lo(c.w), acc[q][6]);
+                  acc[q][7] = fmaf(wgt, bf16_hi(c.w), acc[q][7]);
+                } else {
+                  acc[q][0] = fmaf(wgt, __uint_as_float(c.x), acc[q][0]);
+                  acc[q][1] = fmaf(wgt, __uint_as_float(c.y), acc[q][1]);
+                  acc[q][2] = fmaf(wgt, __uint_as_float(c.z), acc[q][2]);
+                  acc[q][3] = fmaf(wgt, __uint_as_float(c.w), acc[q][3]);
+                }
+              }
+            }
+          }
+        }
+      }
+      __syncthreads();
+    }
+    float4* yt = (float4*)(a.y + t * a.d);
+#pragma unroll
+    for (int q = 0; q < CW; ++q) {
+      if (!cv2[q]) continue;
+#pragma unroll
+      for (int k = 0; k < EPC; k += 4)
+        yt[(c2[q] * EPC + k) / 4] = make_float4(acc[q][k], acc[q][k + 1], acc[q][k + 2], acc[q][k + 3]);
+    }
+  }
+}
+
 // ---------------------------------------------------------------- slot order (no schedule)
 // Where the expert-major order saves no memory traffic, the layer runs the dot in slot order
 // without a schedule: wave v takes slots 2v and 2v + 1, reads their experts and gates and loads
@@ -702,11 +839,18 @@ hipError_t dispatch_dot(int cpl, dim3 grid, hipStream_t st, const DotArgs& a) {
 //     under uniform routing): 2048 tokens on the 2^20-expert tables, 0.611 -> 0.505 ms;
 //   - when the u table fits in half the 256 MB MALL, where a re-read costs no HBM traffic: 4096
 //     tokens on 2^16 experts of d = 512, 0.201 -> 0.148 ms.
+//   - when the u table fits in the MALL at all and experts average at most six tasks, where the
+//     sort costs more than the re-reads (from the MALL): 320^2 experts of d = 1024 (200 MiB), expert
+//     stage with the schedule and in slot order (the faster of the kernels below), K = 512: 256 tokens 154
+//     and 86 us, 512 tokens 235 and 150, 1024 (5.1 tasks per expert) 319 and 296, 1500 (7.5) 424 and 434;
+//     K = 128: 4000 tokens (5.0) 323 and 292, 8000 (10) 553 and 574.
 // With 2.3 tasks per active expert and 4 GiB tables (16384 tokens on 2^20 experts) the schedule
 // pays: 3.54 against 3.64 ms. Each a[p] is summed exactly as expert_dot_kernel sums it, so the
 // two kernels give identical a.
 constexpr int kSlotDotMaxTasks = 8192;
 constexpr int64_t kSlotDotMaxTableBytes = 128ll << 20;
+constexpr int64_t kMallBytes = 256ll << 20;
+constexpr int64_t kSlotDotMallTasks = 6;  // per expert, for tables up to kMallBytes
 
 template <int CPL, bool BF16, bool FULL>
 __global__ __launch_bounds__(256) void slot_dot_kernel(DotArgs a) {
@@ -752,6 +896,25 @@ __global__ __launch_bounds__(256) void slot_dot_kernel(DotArgs a) {
     }
   }
   if (l < G && p0 + l < a.M) a.a[p0 + l] = gv * activation(a.act, hv);
+}
+
+template <bool BF16>
+hipError_t dispatch_token_stage(int cpl, dim3 grid, hipStream_t st, const TokenArgs& a) {
+  const bool full = a.nchunks == cpl * kWave;
+#define OMNIMOE_STAGE(C_)                                                                          \
+  do {                                                                                             \
+    if (full) hipLaunchKernelGGL((token_stage_kernel<C_, BF16, true>), grid, dim3(256), 0, st, a); \
+    else hipLaunchKernelGGL((token_stage_kernel<C_, BF16, false>), grid, dim3(256), 0, st, a);     \
+  } while (0)
+  switch (cpl) {
+    case 1: OMNIMOE_STAGE(1); break;
+    case 2: OMNIMOE_STAGE(2); break;
+    case 4: OMNIMOE_STAGE(4); break;
+    case 8: OMNIMOE_STAGE(8); break;
+    default: OMNIMOE_STAGE(16); break;
+  }
+#undef OMNIMOE_STAGE
+  return hipGetLastError();
 }
 
 template <bool BF16>
@@ -901,8 +1064,11 @@ hipError_t launch_expert_dot(const Shape& s, const void* x, const void* u, const
 bool slot_dot(const Shape& s) {
   const int64_t table = s.N * (int64_t)s.d * (s.bf16 ? 2 : 4);
   return s.M > 0 &&
-         (s.M <= kSlotDotMaxTasks || 2 * s.M <= s.N || table <= kSlotDotMaxTableBytes);
+         (s.M <= kSlotDotMaxTasks || 2 * s.M <= s.N || table <= kSlotDotMaxTableBytes ||
+          (table <= kMallBytes && s.M <= kSlotDotMallTasks * s.N));
 }
+
+bool token_stage(const Shape& s) { return s.T >= 400 || s.T >= 6 * (int64_t)s.hk; }
 
 hipError_t launch_slot_dot(const Shape& s, const void* x, const void* u, const int32_t* idx,
                            const float* gates, float* abuf, hipStream_t st) {
@@ -985,6 +1151,30 @@ hipError_t launch_token_centric(const Shape& s, const void* x, const void* u, co
   const int cpl = chunks_per_lane(a.nchunks);
   return s.bf16 ? dispatch_token<true>(cpl, dim3((unsigned)blocks), st, a)
                 : dispatch_token<false>(cpl, dim3((unsigned)blocks), st, a);
+}
+
+hipError_t launch_token_stage(const Shape& s, const void* x, const void* u, const void* v,
+                              const int32_t* idx, const float* gates, float* y, hipStream_t st) {
+  if (s.T == 0) return hipSuccess;
+  TokenArgs a;
+  a.x = x;
+  a.u = u;
+  a.v = v;
+  a.idx = idx;
+  a.gates = gates;
+  a.y = y;
+  a.T = s.T;
+  a.N = s.N;
+  a.d = s.d;
+  a.hk = s.hk;
+  a.act = s.act;
+  a.nchunks = s.bf16 ? s.d / 8 : s.d / 4;
+  if (a.nchunks < kWave && s.T >= kTokenStageShortRows)
+    return launch_token_centric(s, x, u, v, idx, gates, y, st);
+  const dim3 grid((unsigned)(s.T < 65536 ? s.T : 65536));
+  const int cpl = chunks_per_lane(a.nchunks);
+  return s.bf16 ? dispatch_token_stage<true>(cpl, grid, st, a)
+                : dispatch_token_stage<false>(cpl, grid, st, a);
 }
 
 hipError_t launch_expert_contrib(const Shape& s, const void* x, const void* u, const void* v,

@@ -202,12 +202,18 @@ hipError_t launch_grouped_dot(const Shape& s, const void* x, const void* u, cons
                               const int32_t* n_active, const GroupPlan& plan, float* a,
                               hipStream_t st);
 
-// Where the expert-major order saves no memory traffic (M <= 8192, M <= N / 2, or a u table of
-// at most 128 MiB): a[p] in slot order without a schedule (bf16 or fp32), identical to
+// Where the expert-major order saves no memory traffic (M <= 8192, M <= N / 2, a u table of at
+// most 128 MiB, or one of at most 256 MiB and M <= 6 N): a[p] in slot order without a schedule (bf16 or fp32), identical to
 // launch_expert_dot's a.
 bool slot_dot(const Shape& s);
 hipError_t launch_slot_dot(const Shape& s, const void* x, const void* u, const int32_t* idx,
                            const float* gates, float* abuf, hipStream_t st);
+
+// launch_slot_dot and launch_accumulate in one kernel, a workgroup (or, for many tokens with
+// short rows, a wave) per token, where token_stage(s): the slots summed one after another.
+bool token_stage(const Shape& s);
+hipError_t launch_token_stage(const Shape& s, const void* x, const void* u, const void* v,
+                              const int32_t* idx, const float* gates, float* y, hipStream_t st);
 
 // y[t] = sum over slots (h, k) in order of a[p] * v[idx[p]].
 hipError_t launch_accumulate(const Shape& s, const void* v, const int32_t* idx, const float* a,

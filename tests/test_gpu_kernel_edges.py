@@ -177,3 +177,41 @@ def test_f32_logits(case):
     for keys, xq, got in ((kr, x[:, :dk], hs[..., :nr]), (kc, x[:, c0:c0 + dk], hs[..., nr:])):
         ref = np.einsum("tm,hjm->thj", xq.astype(np.float64), keys.astype(np.float64))
         assert np.all(np.abs(got.cpu().numpy() - ref) <= higham_bound(xq, keys) + 1e-30)
+
+
+# (T, d, n_rows, n_cols, H, K, dtype, act, one kernel?): the expert stage by tokens in the layer: both sides of its line (400
+# tokens, or six per slot), slots that four waves do not share evenly and more than one batch of 256, rows of one to
+# eight chunks a lane, whole and partial; short rows with one wave per token from 2048 tokens on; tables past 128 MiB on
+# both sides of six tasks per expert.
+STAGE_CASES = [(48, 64, 16, 17, 1, 8, "f32", "gelu", True), (47, 64, 16, 17, 1, 8, "f32", "gelu", False),
+               (400, 520, 12, 13, 3, 13, "f32", "silu", True), (399, 512, 30, 40, 3, 27, "bf16", "gelu", False),
+               (401, 1024, 20, 21, 2, 150, "bf16", "gelu", True), (2048, 200, 10, 10, 2, 5, "bf16", "gelu", True),
+               (2047, 200, 10, 10, 2, 5, "bf16", "silu", True), (500, 2048, 9, 10, 5, 3, "bf16", "gelu", True),
+               (430, 4096, 5, 6, 1, 3, "f32", "gelu", True), (450, 2056, 7, 9, 2, 3, "bf16", "gelu", True),
+               (600, 4096, 128, 129, 2, 82, "bf16", "gelu", True), (608, 4096, 128, 129, 2, 82, "bf16", "gelu", False)]
+
+
+@pytest.mark.parametrize("case", STAGE_CASES, ids=[str(c) for c in STAGE_CASES])
+def test_token_stage_layer(case):
+    T, d, nr, nc, H, K, dtype, act, one = case
+    say(f"[token stage] {case}")
+    w = synth.Workload("stage", T=T, d=d, n_rows=nr, n_cols=nc, d_key=16, H=H, K=K, dtype=dtype, act=act)
+    inp = synth.make_inputs(w)
+    dev, D = upload(inp), B.make_desc(w)
+    assert not one or not B.omnimoe_layer_path(D) & B.PATH_SCHEDULE
+    y = torch.full((T, d), float("nan"), device="cuda")
+    idx = torch.empty((T, H, K), dtype=torch.int32, device="cuda")
+    g = torch.empty((T, H, K), device="cuda")
+    P.omnimoe_layer_forward(D, dev["x"], dev["keys_row"], dev["keys_col"], dev["u"], dev["v"], y, idx, g)
+    y_tc = torch.full((T, d), float("nan"), device="cuda")
+    P.omnimoe_expert_forward_token_centric(D, dev["x"], dev["u"], dev["v"], idx, g, y_tc)
+    torch.cuda.synchronize()
+    f = {k: synth.as_f32(v) for k, v in inp.items()}
+    gi, gg = idx.cpu().numpy(), g.cpu().numpy()
+    dsc = oracle.desc(w)
+    ref = oracle.expert_forward(dsc, f["x"], f["u"], f["v"], gi, gg.astype(np.float64))
+    # fp32 sums of exact products: Higham's bounds through the activation (as for the routed sum above)
+    got = y.cpu().numpy()
+    assert np.all(np.abs(got.astype(np.float64) - ref) <= grouped_gap_bound(f, gi, gg, d, dsc.act))
+    if one:  # the same dots and the same slot order
+        assert np.array_equal(got.view(np.uint8), y_tc.cpu().numpy().view(np.uint8))
