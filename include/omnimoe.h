@@ -310,7 +310,12 @@ omnimoe_status omnimoe_route_backward(const omnimoe_layer_desc* desc, const void
  * cache, or of at most 256 MiB with at most six tasks per expert), no schedule is formed: the same
  * a_p are computed in slot order, with identical results (by the selection kernel itself when there
  * are at least 256 (token, head) rows, or, with enough tokens, in one kernel with the routed sum,
- * whose time OMNIMOE_KERNEL_ACCUMULATE then holds; omnimoe_layer_path tells which kernels run). With one head, K >= N / 64 and group_size 1,
+ * whose time OMNIMOE_KERNEL_ACCUMULATE then holds; omnimoe_layer_path tells which kernels run).
+ * With at least 512 tokens, two tasks per expert and tables of at most 256 MiB whose rows are 2, 4
+ * or 8 KiB, every token's tasks are put in one order of the experts instead and swept by all tokens
+ * together (OMNIMOE_KERNEL_SCHEDULE times that ordering): the sums run in another fixed order, so y
+ * matches omnimoe_expert_forward's to fp32 rounding; with groups of B > 1 this holds for the routed
+ * sum. With one head, K >= N / 64 and group_size 1,
  * both products run dense over all experts (Eq. 14 with a single group): x . u for every
  * (token, expert) pair, gate and activation kept at the selected pairs (a_p rounded to bf16),
  * then y = A V; no schedule is formed. Workspace:
@@ -326,8 +331,9 @@ omnimoe_status omnimoe_layer_forward(const omnimoe_layer_desc* desc, const void*
  * *path receives an OR of the flags below. OMNIMOE_ERR_INVALID_ARG for a bad descriptor or a
  * NULL path. The result depends only on the descriptor, so it can be taken once per shape. */
 typedef enum {
-  OMNIMOE_PATH_SCHEDULE = 1,   /* the expert-major schedule is formed (Eq. 12-13); without it the
-                                  a_p are formed in slot order */
+  OMNIMOE_PATH_SCHEDULE = 1,   /* the tasks are put in expert order: the expert-major schedule
+                                  (Eq. 12-13), or each token's tasks for the sweeps; without it
+                                  the a_p are formed in slot order */
   OMNIMOE_PATH_GROUPED = 2,    /* a_p from the grouped GEMM of Eq. 14 (group_size > 1) */
   OMNIMOE_PATH_SELECT_DOT = 4, /* the selection kernel also forms the slot-order a_p (no separate
                                   dot launch; the OMNIMOE_KERNEL_SELECT time includes it) */

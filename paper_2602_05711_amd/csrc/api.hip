@@ -106,6 +106,39 @@ constexpr int64_t kSortFreeMinTasks = 8192;
 // The slot-order dot and the routed sum in one kernel (not among the reported flags: like them it
 // forms no schedule).
 constexpr int32_t kPathTokenStage = 1 << 16;
+// Dots and sum, or with groups the sum, in sweeps over the experts (the tasks of every token are put
+// in an order of the experts first: reported as a schedule).
+constexpr int32_t kPathSweepStage = 1 << 17;
+constexpr int32_t kPathSweepSum = 1 << 18;
+constexpr int32_t kPathReported = (1 << 16) - 1;
+
+// The sweeps pay from two tasks per expert and 512 tokens on. Expert stage on 320^2 experts of
+// d = 1024 (us, the former kernels and the sweeps): K = 128 (1.3 tasks per expert at 1024
+// tokens) 78 and 84, 2048 tokens 157 and 132, 16384 tokens 1024 and 785; K = 512: 400 tokens 130 and 135,
+// 512 tokens 152 and 137, 1024 tokens 298 and 199, 4096 tokens 972 and 582. 64 slots on 6 10^4 experts: 1024
+// tokens 44 and 47, 2048 tokens 82 and 75; on 10^4: 1024 tokens 37 and 27; on 4 10^4 of d = 2048:
+// 1024 tokens 83 and 73.
+bool sweep_pays(const Shape& s) {
+  return omnimoe::sweepable(s) && s.T >= 512 && s.M >= 2 * s.N;
+}
+
+size_t sched_or_plan_bytes(const Shape& s);
+
+// Layer workspace behind the fixed buffers without and with the sweeps. A shape that the sweeps
+// would take past the static scratch of omnimoe_layer_forward_noalloc keeps the former kernels.
+size_t late_bytes(const Shape& s) {
+  return sched_or_plan_bytes(s) + m_bytes(s) + omnimoe::dense_accumulate_ws_bytes(s);
+}
+size_t fixed_bytes(const Shape& s) { return 3 * m_bytes(s) + 2 * active_bytes(s) + 256; }
+bool sweep_fits(const Shape& s, size_t late) {
+  const size_t limit = (size_t)OMNIMOE_NOALLOC_SCRATCH_BYTES;
+  return fixed_bytes(s) + std::max(hs_bytes(s), late) <= limit ||
+         fixed_bytes(s) + std::max(hs_bytes(s), late_bytes(s)) > limit;
+}
+size_t sweep_sum_late_bytes(const Shape& s) {
+  return sched_or_plan_bytes(s) + m_bytes(s) + omnimoe::sweep_sum_ws_bytes(s);
+}
+
 int32_t layer_path(const Shape& s) {
   const bool grouped = layer_grouped(s);
   const bool unscheduled = !grouped && omnimoe::slot_dot(s);
@@ -118,6 +151,11 @@ int32_t layer_path(const Shape& s) {
   if (unscheduled && !(f & (OMNIMOE_PATH_SELECT_DOT | OMNIMOE_PATH_DENSE_SUM)) &&
       omnimoe::token_stage(s))
     f |= kPathTokenStage;
+  if (!(f & (OMNIMOE_PATH_SELECT_DOT | OMNIMOE_PATH_DENSE_SUM)) && sweep_pays(s)) {
+    if (grouped && sweep_fits(s, sweep_sum_late_bytes(s))) f |= kPathSweepSum;
+    if (!grouped && sweep_fits(s, omnimoe::sweep_stage_ws_bytes(s)))
+      f = OMNIMOE_PATH_SCHEDULE | kPathSweepStage;
+  }
   // Both products dense over all experts: no schedule and no per-task dot.
   if (omnimoe::dense_dot(s)) f = OMNIMOE_PATH_DENSE_SUM | OMNIMOE_PATH_DENSE_DOT;
   return f;
@@ -168,15 +206,17 @@ size_t stage_bytes(const Shape& s, int stage) {
       // idx, gates, perm, active, active_offsets, n_active, then the logits (dead after
       // selection) overlapped with the sort buffers, the a[] buffer and the dense routed sum's
       // buffers.
-      size_t fixed = 3 * m_bytes(s) + 2 * active_bytes(s) + 256;
-      size_t late = sched_or_plan_bytes(s) + m_bytes(s) + omnimoe::dense_accumulate_ws_bytes(s);
+      size_t late = late_bytes(s);
       // A selection kernel that forms a[] writes it while other rows' logits are still being
       // read: a[] and the dense sum's buffers then follow the logits instead of sharing them.
       if (layer_path(s) & OMNIMOE_PATH_SELECT_DOT)
         late = hs_bytes(s) + m_bytes(s) + omnimoe::dense_accumulate_ws_bytes(s);
       // Both products dense: only their buffers, after the logits are dead.
       if (layer_path(s) & OMNIMOE_PATH_DENSE_DOT) late = omnimoe::dense_dot_ws_bytes(s);
-      return fixed + std::max(hs_bytes(s), late);
+      // The sweeps: their list (and partial dots) after the logits are dead; with groups, after a[].
+      if (layer_path(s) & kPathSweepStage) late = omnimoe::sweep_stage_ws_bytes(s);
+      if (layer_path(s) & kPathSweepSum) late = sweep_sum_late_bytes(s);
+      return fixed_bytes(s) + std::max(hs_bytes(s), late);
     }
   }
 }
@@ -250,6 +290,16 @@ omnimoe_status layer_impl(const omnimoe_layer_desc* desc, const void* x, const v
     if (timer) ++timer->used;
     return OMNIMOE_OK;
   }
+  if (path & kPathSweepStage) {
+    if ((e = omnimoe::launch_sweep_order(s, idx, late, strm))) return hip_status(e);
+    mark(3);
+    if ((e = omnimoe::launch_sweep_dot(s, x, u, gates, late, strm))) return hip_status(e);
+    mark(4);
+    if ((e = omnimoe::launch_sweep_sorted_sum(s, v, y, late, strm))) return hip_status(e);
+    mark(5);
+    if (timer) ++timer->used;
+    return OMNIMOE_OK;
+  }
   const int32_t* sk = nullptr;
   const int32_t* gk = nullptr;
   if (!unscheduled) {
@@ -287,7 +337,10 @@ omnimoe_status layer_impl(const omnimoe_layer_desc* desc, const void* x, const v
     return hip_status(e);
   }
   mark(4);
-  if ((e = routed_sum(s, v, idx, abuf, y, (char*)abuf + m_bytes(s), strm))) return hip_status(e);
+  void* const sum_ws = (char*)abuf + m_bytes(s);
+  e = path & kPathSweepSum ? omnimoe::launch_sweep_sum(s, v, idx, abuf, y, sum_ws, strm)
+                           : routed_sum(s, v, idx, abuf, y, sum_ws, strm);
+  if (e) return hip_status(e);
   mark(5);
   if (timer) ++timer->used;
   return OMNIMOE_OK;
@@ -649,7 +702,7 @@ omnimoe_status omnimoe_layer_path(const omnimoe_layer_desc* desc, int32_t* path)
   omnimoe_status st = check_desc(desc, &s);
   if (st) return st;
   if (!path) return OMNIMOE_ERR_INVALID_ARG;
-  *path = layer_path(s) & ~kPathTokenStage;
+  *path = layer_path(s) & kPathReported;
   return OMNIMOE_OK;
 }
 
