@@ -318,14 +318,53 @@ __device__ __noinline__ uint64_t half_topk_batched(const float* __restrict__ p, 
   return best;
 }
 
+// The slot-order dots of picks k0 <= k < k1 of one row (expert of pick k on lane k of eid): the u
+// rows four at a time against the token row xr, each product summed exactly as slot_dot_kernel
+// sums it. Lane k gets x . u of pick k.
+template <int DCPL>
+__device__ __forceinline__ float pick_dots(const SelectArgs& a, const uint4 (&xr)[DCPL], int eid,
+                                           int k0, int k1) {
+  typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
+  const uint4* U = (const uint4*)a.u;
+  const int l = lane_id();
+  float hv = 0.0f;
+  for (int j0 = k0; j0 < k1; j0 += 4) {
+    uint4 ur[4][DCPL];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      int ei = readlane_i32(eid, j0 + i < k1 ? j0 + i : k1 - 1);
+      ei = ei < 0 ? 0 : (ei >= a.N ? (int)(a.N - 1) : ei);
+      const u32x4_t* ub = (const u32x4_t*)(U + (int64_t)ei * (DCPL * kWave));
+#pragma unroll
+      for (int q = 0; q < DCPL; ++q) {
+        const u32x4_t v = __builtin_nontemporal_load(ub + l + kWave * q);
+        ur[i][q] = make_uint4(v.x, v.y, v.z, v.w);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      float acc = 0.0f;
+#pragma unroll
+      for (int q = 0; q < DCPL; ++q) acc = chunk_dot<true>(ur[i][q], xr[q], acc);
+      const float hs = wave_sum_uniform(acc);
+      if (l == j0 + i) hv = hs;
+    }
+  }
+  return hv;
+}
+
 // DCPL > 0: after a row's picks and gates, the same wave forms their a[p] in slot order (the
-// layer's dot where it forms no schedule): the token row once, then the u rows four at a time,
-// each product summed exactly as slot_dot_kernel sums it, so a[p] is the same on both paths.
-// This saves the dot's launch and its reads of idx and gates at a decode step.
-template <int R, bool VEC, bool FULL, int DCPL = 0>
+// layer's dot where it forms no schedule): the token row once, then the u rows four at a time, so
+// a[p] is the same as slot_dot_kernel's. This saves the dot's launch and its reads of idx and gates
+// at a decode step. TEAM: a workgroup per row (grid.x = rows); wave 0 selects, and its four waves
+// then share the row's picks, so that K = 16 picks' u rows are in flight at once instead of four after
+// four; for the few rows that leave the chip's waves idle (kTeamMaxRows).
+template <int R, bool VEC, bool FULL, int DCPL = 0, bool TEAM = false>
 __global__ __launch_bounds__(256) void select_kernel(SelectArgs a) {
   __shared__ uint64_t lists[4][2][kWave];  // per wave: sorted row keys, sorted column keys
   __shared__ uint64_t stage[4][kWave];     // per wave: survivors, rows at 0, columns at 32
+  __shared__ int team_e[TEAM ? kWave : 1];      // the row's picks and gates for all waves
+  __shared__ float team_g[TEAM ? kWave : 1];
   const int K = a.K;
   const int kr = K < a.nr ? K : a.nr;
   const int kc = K < a.nc ? K : a.nc;
@@ -336,8 +375,15 @@ __global__ __launch_bounds__(256) void select_kernel(SelectArgs a) {
   uint64_t* rowk = lists[w][0];
   uint64_t* colk = lists[w][1];
   uint64_t* st = stage[w];
-  const int64_t stride = (int64_t)gridDim.x * 4;
-  int64_t row = (int64_t)blockIdx.x * 4 + w;
+  const int64_t stride = TEAM ? a.rows : (int64_t)gridDim.x * 4;
+  int64_t row = TEAM ? (w == 0 ? (int64_t)blockIdx.x : a.rows) : (int64_t)blockIdx.x * 4 + w;
+  // TEAM: the token row, while wave 0 selects
+  [[maybe_unused]] uint4 xt[TEAM ? DCPL : 1];
+  if constexpr (TEAM) {
+    const uint4* X = (const uint4*)a.x + (blockIdx.x / (unsigned)a.H) * (int64_t)(DCPL * kWave);
+#pragma unroll
+    for (int q = 0; q < DCPL; ++q) xt[q] = X[l + kWave * q];
+  }
   // The next row's logits are loaded while the current row is processed.
   float vr[R], vc[R];
   if (row < a.rows) {
@@ -405,37 +451,16 @@ __global__ __launch_bounds__(256) void select_kernel(SelectArgs a) {
       a.idx[row * K + l] = (int32_t)(0xFFFFFFFFu - best.nn);
       a.gates[row * K + l] = e / z;
     }
-    if constexpr (DCPL > 0) {
-      typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
+    if constexpr (TEAM) {
+      team_e[l] = (int)(0xFFFFFFFFu - best.nn);
+      team_g[l] = e / z;
+    } else if constexpr (DCPL > 0) {
       const uint4* X = (const uint4*)a.x + (row / a.H) * (int64_t)(DCPL * kWave);
-      const uint4* U = (const uint4*)a.u;
       const int eid = (int)(0xFFFFFFFFu - best.nn);  // lane k < K: the k-th pick
       uint4 xr[DCPL];
 #pragma unroll
       for (int q = 0; q < DCPL; ++q) xr[q] = X[l + kWave * q];
-      float hv = 0.0f;
-      for (int j0 = 0; j0 < K; j0 += 4) {
-        uint4 ur[4][DCPL];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          int ei = readlane_i32(eid, j0 + i < K ? j0 + i : K - 1);
-          ei = ei < 0 ? 0 : (ei >= a.N ? (int)(a.N - 1) : ei);
-          const u32x4_t* ub = (const u32x4_t*)(U + (int64_t)ei * (DCPL * kWave));
-#pragma unroll
-          for (int q = 0; q < DCPL; ++q) {
-            const u32x4_t v = __builtin_nontemporal_load(ub + l + kWave * q);
-            ur[i][q] = make_uint4(v.x, v.y, v.z, v.w);
-          }
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          float acc = 0.0f;
-#pragma unroll
-          for (int q = 0; q < DCPL; ++q) acc = chunk_dot<true>(ur[i][q], xr[q], acc);
-          const float hs = wave_sum_uniform(acc);
-          if (l == j0 + i) hv = hs;
-        }
-      }
+      const float hv = pick_dots<DCPL>(a, xr, eid, 0, K);
       if (l < K) a.abuf[row * K + l] = (e / z) * activation(a.act, hv);
     }
 #pragma unroll
@@ -443,6 +468,14 @@ __global__ __launch_bounds__(256) void select_kernel(SelectArgs a) {
       vr[k] = nr_[k];
       vc[k] = nc_[k];
     }
+  }
+  if constexpr (TEAM) {
+    __syncthreads();
+    const int per = (K + 3) / 4, k0 = w * per, k1 = k0 + per < K ? k0 + per : K;
+    if (k0 >= k1) return;
+    const float hv = pick_dots<DCPL>(a, xt, team_e[l], k0, k1);
+    if (l >= k0 && l < k1)
+      a.abuf[(int64_t)blockIdx.x * K + l] = team_g[l] * activation(a.act, hv);
   }
 }
 
@@ -1179,6 +1212,11 @@ hipError_t launch_select(const Shape& s, const float* half_scores, int32_t* idx,
   return hipGetLastError();
 }
 
+// Rows up to which a workgroup takes one row: layer call on the 2^20-expert tables with a wave and
+// with a workgroup per row, 256 rows 28.2 and 25.0 us, 512 rows 32.8 and 31.5, 800 rows 59.8 and 65.4 (the
+// waves that wait for the selection hold the registers of a row that could be selected).
+constexpr int64_t kTeamMaxRows = 512;
+
 bool select_dot_fusable(const Shape& s) {
   const int nchunks = s.d / 8;
   const bool rows_ok = s.nr == s.nc && (s.nr == 256 || s.nr == 512 || s.nr == 1024);
@@ -1205,21 +1243,28 @@ hipError_t launch_select_dot(const Shape& s, const float* half_scores, int32_t* 
   a.N = s.N;
   a.H = s.H;
   a.act = s.act;
-  int64_t blocks = (s.rows + 3) / 4;
+  const bool team = s.rows <= kTeamMaxRows;
+  int64_t blocks = team ? s.rows : (s.rows + 3) / 4;
   if (blocks > 8192) blocks = 8192;
   const dim3 grid((unsigned)blocks), block(256);
   const int cpl = s.d / 8 / kWave;
-#define OMNIMOE_SELECT_DOT(R_)                                                                 \
-  do {                                                                                         \
-    if (cpl == 1) hipLaunchKernelGGL((select_kernel<R_, true, true, 1>), grid, block, 0, st, a);      \
-    else if (cpl == 2) hipLaunchKernelGGL((select_kernel<R_, true, true, 2>), grid, block, 0, st, a); \
-    else if (cpl == 4) hipLaunchKernelGGL((select_kernel<R_, true, true, 4>), grid, block, 0, st, a); \
-    else hipLaunchKernelGGL((select_kernel<R_, true, true, 8>), grid, block, 0, st, a);               \
+#define OMNIMOE_SELECT_DOT_T(R_, T_)                                                                  \
+  do {                                                                                                \
+    if (cpl == 1) hipLaunchKernelGGL((select_kernel<R_, true, true, 1, T_>), grid, block, 0, st, a);      \
+    else if (cpl == 2) hipLaunchKernelGGL((select_kernel<R_, true, true, 2, T_>), grid, block, 0, st, a); \
+    else if (cpl == 4) hipLaunchKernelGGL((select_kernel<R_, true, true, 4, T_>), grid, block, 0, st, a); \
+    else hipLaunchKernelGGL((select_kernel<R_, true, true, 8, T_>), grid, block, 0, st, a);               \
+  } while (0)
+#define OMNIMOE_SELECT_DOT(R_)                 \
+  do {                                         \
+    if (team) OMNIMOE_SELECT_DOT_T(R_, true);  \
+    else OMNIMOE_SELECT_DOT_T(R_, false);      \
   } while (0)
   if (s.nr == 256) OMNIMOE_SELECT_DOT(4);
   else if (s.nr == 512) OMNIMOE_SELECT_DOT(8);
   else OMNIMOE_SELECT_DOT(16);
 #undef OMNIMOE_SELECT_DOT
+#undef OMNIMOE_SELECT_DOT_T
   return hipGetLastError();
 }
 

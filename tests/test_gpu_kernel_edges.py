@@ -256,3 +256,37 @@ def test_sweep_layer(case):
     say(f"  max err / bound {ratio.max():.3f}")
     assert ratio.max() <= 1.0
     assert np.array_equal(ys[0].view(np.uint8), ys[1].view(np.uint8))
+
+
+# (T, n, d, H, K): the selection that forms the dot with a workgroup per row (up to 512 rows) and with a wave per row past it; picks
+# that four waves share evenly, unevenly, and fewer picks than waves.
+TEAM_CASES = [(64, 256, 512, 4, 16), (512, 256, 512, 1, 13), (513, 256, 512, 1, 13), (128, 512, 1024, 3, 64),
+              (300, 256, 2048, 1, 3), (65, 1024, 512, 4, 1), (256, 256, 4096, 2, 30)]
+
+
+@pytest.mark.parametrize("case", TEAM_CASES, ids=[str(c) for c in TEAM_CASES])
+def test_selection_dot_team(case):
+    T, n, d, H, K = case
+    say(f"[selection dot] {case}")
+    w = synth.Workload("team", T=T, d=d, n_rows=n, n_cols=n, d_key=64, H=H, K=K)
+    inp = synth.make_inputs(w)
+    dev, D = upload(inp), B.make_desc(w)
+    assert B.omnimoe_layer_path(D) & B.PATH_SELECT_DOT
+    y = torch.full((T, d), float("nan"), device="cuda")
+    idx = torch.empty((T, H, K), dtype=torch.int32, device="cuda")
+    g = torch.empty((T, H, K), device="cuda")
+    P.omnimoe_layer_forward(D, dev["x"], dev["keys_row"], dev["keys_col"], dev["u"], dev["v"], y, idx, g)
+    # the stage on its own (the separate dot kernel) on the layer's routing: the same bits
+    perm = torch.empty(w.M, dtype=torch.int32, device="cuda")
+    cap = min(w.M, w.N)
+    act = torch.empty(cap, dtype=torch.int32, device="cuda")
+    off = torch.empty(cap + 1, dtype=torch.int32, device="cuda")
+    na = torch.empty(1, dtype=torch.int32, device="cuda")
+    P.omnimoe_schedule(D, idx, perm, act, off, na)
+    y2 = torch.full((T, d), float("nan"), device="cuda")
+    P.omnimoe_expert_forward(D, dev["x"], dev["u"], dev["v"], idx, g, perm, y2)
+    idx2, g2 = torch.empty_like(idx), torch.empty_like(g)
+    P.omnimoe_route(D, dev["x"], dev["keys_row"], dev["keys_col"], idx2, g2)
+    torch.cuda.synchronize()
+    assert torch.equal(idx, idx2) and torch.equal(g, g2)
+    assert np.array_equal(y.cpu().numpy().view(np.uint8), y2.cpu().numpy().view(np.uint8))
