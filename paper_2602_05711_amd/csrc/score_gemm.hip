@@ -7,7 +7,8 @@
 // product (x . u for every (token, expert) pair, g * act kept at the selected pairs only).
 //
 // bf16, d_key % 64 == 0: 256 x 256 tile, eight waves of 128 x 64 on v_mfma_f32_32x32x16_bf16,
-//   operands copied global -> LDS without registers (two 64 KiB stages, XOR-swizzled rows);
+//   operands copied global -> LDS without registers (two 64 KiB stages, XOR-swizzled rows); 128 x 128,
+//   128 x 64 or 64 x 64 tiles of four waves where those leave compute units without a tile;
 // bf16, one to four tokens, d_key = 128 * 2^k <= 2048: sixteen lanes per key row with coalesced
 //   loads and v_dot2_f32_bf16 (no MFMA);
 // bf16, at most 64 tokens, d_key % 256 == 0: a split-K decode kernel with the token rows in LDS
@@ -201,6 +202,10 @@ typedef __attribute__((address_space(3))) void* lds_ptr_t;
 __device__ __forceinline__ int swz(int r) { return (r >> 1) & 7; }
 
 __device__ __forceinline__ void wait_vm0() { __builtin_amdgcn_s_waitcnt(0x0F70); }  // vmcnt(0)
+template <int N>
+__device__ __forceinline__ void wait_vm() {  // vmcnt(N)
+  __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
+}
 
 // Epilogue of the masked-activation product (the first product of Eq. 14 over all experts).
 // Only the selected cells of a tile (a few percent in the layers that take this product) need
@@ -478,6 +483,116 @@ __global__ __launch_bounds__(512, 1) void score_bf16_large_kernel(ScoreArgs a) {
   };
   if (m0 + LM <= a.T) store_all([](int) { return true; });
   else store_all([&](int r) { return m_lane + r < a.T; });
+}
+
+// ---------------------------------------------------------------- mid-size bf16 kernel
+// The large kernel's products on TM x TN tiles of four waves (2 x 2, each TM / 2 x TN / 2), for
+// launches whose 256 x 256 tiles leave compute units without one. A ring of NS stages of 64-wide
+// k steps (same swizzled rows): at step kt a wave waits until its own copies of that stage are done,
+// the barrier makes everyone's visible and the stage before free, and the copies of step kt + NS - 1
+// go into that one. Each element's products are added in the same order as in the large kernel, so the
+// logits are the same.
+template <bool ACC, int TM, int TN, int NS>
+__global__ __launch_bounds__(256, 2) void score_bf16_mid_kernel(ScoreArgs a) {
+  constexpr int MI = TM / 64, NJ = TN / 64;          // 32 x 32 tiles per wave
+  constexpr int kStage = (TM + TN) * LROW;
+  constexpr int LA = TM / 32, LB = TN / 32;          // copies per wave: rows 8 (w LA + i) .. + 8
+  const int half = blockIdx.z;
+  const int ncols = a.H * a.nh[half];
+  const int n0 = blockIdx.x * TN;
+  if (n0 >= ncols) return;
+  const int64_t m0 = (int64_t)blockIdx.y * TM;
+  const uint16_t* X = (const uint16_t*)a.x;
+  const uint16_t* Kt = (const uint16_t*)a.keys[half];
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  const int wm = wid >> 1, wn = wid & 1;
+  const uint16_t* ga[LA];
+  const uint16_t* gb[LB];
+#pragma unroll
+  for (int i = 0; i < LA; ++i) {
+    const int r = (wid * LA + i) * 8 + (lane >> 3);
+    int64_t gm = m0 + r;
+    if (gm >= a.T) gm = a.T - 1;
+    ga[i] = X + gm * a.d + a.col0[half] + ((lane & 7) ^ swz(r)) * 8;
+  }
+#pragma unroll
+  for (int i = 0; i < LB; ++i) {
+    const int r = (wid * LB + i) * 8 + (lane >> 3);
+    int gn = n0 + r;
+    if (gn >= ncols) gn = ncols - 1;
+    gb[i] = Kt + (int64_t)gn * a.dk + ((lane & 7) ^ swz(r)) * 8;
+  }
+  auto issue = [&](int stage, int k0) {
+    unsigned char* base = smem + stage * kStage;
+#pragma unroll
+    for (int i = 0; i < LA; ++i)
+      __builtin_amdgcn_global_load_lds((const void*)(ga[i] + k0),
+                                       (lds_ptr_t)(base + (wid * LA + i) * 8 * LROW), 16, 0, 0);
+#pragma unroll
+    for (int i = 0; i < LB; ++i)
+      __builtin_amdgcn_global_load_lds((const void*)(gb[i] + k0),
+                                       (lds_ptr_t)(base + (TM + (wid * LB + i) * 8) * LROW), 16, 0, 0);
+  };
+  f32x16 acc[MI][NJ];
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+      for (int q = 0; q < 16; ++q) acc[i][j][q] = 0.f;
+  const int KT = a.dk / LK;
+  const int frow = lane & 31, fk = lane >> 5, sw = swz(frow);
+  auto frag = [&](const unsigned char* st, int row, int ks) -> bf16x8 {
+    return *(const bf16x8*)(st + (row + frow) * LROW + (((ks * 2 + fk) ^ sw) << 4));
+  };
+#pragma unroll
+  for (int s = 0; s < NS - 1; ++s)
+    if (s < KT) issue(s, s * LK);
+  int stage = 0;
+  for (int kt = 0; kt < KT; ++kt) {
+    // copies of the NS - 2 later steps may still be in flight
+    if (kt + NS - 1 <= KT) wait_vm<(NS - 2) * (LA + LB)>();
+    else wait_vm0();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    const int nx = stage == 0 ? NS - 1 : stage - 1;  // (kt + NS - 1) % NS
+    if (kt + NS - 1 < KT) issue(nx, (kt + NS - 1) * LK);
+    const unsigned char* st = smem + stage * kStage;
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      bf16x8 fa[MI], fb[NJ];
+#pragma unroll
+      for (int i = 0; i < MI; ++i) fa[i] = frag(st, wm * (TM / 2) + i * 32, ks);
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) fb[j] = frag(st, TM + wn * (TN / 2) + j * 32, ks);
+#pragma unroll
+      for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
+    }
+    stage = stage + 1 == NS ? 0 : stage + 1;
+  }
+  const int64_t m_lane = m0 + wm * (TM / 2) + (lane >> 5) * 4;
+  const bool whole = m0 + TM <= a.T;
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) {
+    const int n = n0 + wn * (TN / 2) + j * 32 + (lane & 31);
+    if (n >= ncols) continue;
+    float* const orow = a.out + m_lane * a.ldo + out_col(a, half, n);
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int q = 0; q < 16; ++q) {
+        const int r = i * 32 + (q >> 2) * 8 + (q & 3);
+        if (!whole && m_lane + r >= a.T) continue;
+        float* const o = orow + (int64_t)r * a.ldo;
+        if constexpr (ACC) *o += acc[i][j][q];
+        else __builtin_nontemporal_store(acc[i][j][q], o);
+      }
+  }
 }
 
 // ---------------------------------------------------------------- few-token bf16 kernel
@@ -924,6 +1039,31 @@ constexpr int64_t kPrefetchMaxBytes = 128ll << 20;  // half the MALL
 // (2048) 1876 and 1901, 16384 (4096) 3480 and 3561.
 constexpr int64_t kPrefetchMinTiles = 1024;
 
+// Workgroups of both halves with tm x tn tiles.
+int64_t tiles_of(const Shape& s, int tm, int tn) {
+  return ((s.T + tm - 1) / tm) * (((int64_t)s.H * s.nr + tn - 1) / tn +
+                                  ((int64_t)s.H * s.nc + tn - 1) / tn);
+}
+
+// The largest tile that still fills the chip's 256 compute units. Logits of 2 x 8192 keys, d_key =
+// 1024 (us on 256 x 256, 128 x 128, 128 x 64 and 64 x 64 tiles): 100 tokens (64, 128, 256, 512
+// workgroups) 32.2, 15.4, 11.8, 10.0; 200 tokens (64, 256, 512, 1024) 33.2, 16.9, 15.9, 18.8; 509
+// tokens (128, 512, 1024, 2048) 35.4, 25.1, 30.9, 33.5; at 768 tokens (192 large tiles) the large kernel is the
+// fastest. 2 x 1024 keys, d_key = 256: 2048 tokens (64, 256, 512, 1024) 15.0, 10.2, 9.4, 8.7; 4096 tokens
+// (128, 512, ...) 15.1, 12.5, 14.8, 13.1. Shared branch, d = d_ff = 2048: 100 tokens 132, 66, 47, 32; 2048
+// tokens 148, 93, 93, 108.
+constexpr int64_t kLargeMinTiles = 192, kMid128MinTiles = 384, kMid64MinTiles = 512;
+
+template <int TM, int TN, int NS>
+void launch_mid(const ScoreArgs& a, int ncols, bool accumulate, hipStream_t st) {
+  const dim3 grid((unsigned)((ncols + TN - 1) / TN), (unsigned)((a.T + TM - 1) / TM), 2);
+  constexpr size_t lds = (size_t)NS * (TM + TN) * LROW;
+  if (accumulate)
+    hipLaunchKernelGGL((score_bf16_mid_kernel<true, TM, TN, NS>), grid, dim3(256), lds, st, a);
+  else
+    hipLaunchKernelGGL((score_bf16_mid_kernel<false, TM, TN, NS>), grid, dim3(256), lds, st, a);
+}
+
 hipError_t launch_score(const Shape& s, const void* x, const void* keys_row,
                         const void* keys_col, float* half_scores, hipStream_t st,
                         bool accumulate) {
@@ -959,9 +1099,7 @@ hipError_t launch_score(const Shape& s, const void* x, const void* keys_row,
     pa.n[1] = (int64_t)s.H * s.nr * s.dk * 2 / 16;
     pa.n[2] = (int64_t)s.H * s.nc * s.dk * 2 / 16;
     pa.sink = (uint32_t*)half_scores;
-    const int64_t tiles = ((s.T + LM - 1) / LM) * (((int64_t)s.H * s.nr + LN - 1) / LN +
-                                                   ((int64_t)s.H * s.nc + LN - 1) / LN);
-    if (tiles >= kPrefetchMinTiles && (pa.n[0] + pa.n[1] + pa.n[2]) * 16 <= kPrefetchMaxBytes)
+    if (tiles_of(s, LM, LN) >= kPrefetchMinTiles && (pa.n[0] + pa.n[1] + pa.n[2]) * 16 <= kPrefetchMaxBytes)
       hipLaunchKernelGGL(prefetch_kernel, dim3(4096), dim3(256), 0, st, pa);
   }
   if (s.bf16 && s.T >= 8 && s.T <= 64 && s.dk % 256 == 0 && s.dk <= 1024) {
@@ -1034,6 +1172,10 @@ hipError_t launch_score(const Shape& s, const void* x, const void* keys_row,
     else OMNIMOE_SKINNY_STEPS(false, 1);
 #undef OMNIMOE_SKINNY_STEPS
 #undef OMNIMOE_SKINNY
+  } else if (s.bf16 && s.dk % LK == 0 && tiles_of(s, LM, LN) < kLargeMinTiles) {
+    if (tiles_of(s, 128, 128) >= kMid128MinTiles) launch_mid<128, 128, 2>(a, ncols, accumulate, st);
+    else if (tiles_of(s, 128, 64) >= kMid64MinTiles) launch_mid<128, 64, 3>(a, ncols, accumulate, st);
+    else launch_mid<64, 64, 3>(a, ncols, accumulate, st);
   } else if (s.bf16 && s.dk % LK == 0) {
     dim3 grid((ncols + LN - 1) / LN, (unsigned)((s.T + LM - 1) / LM), 2);
     if (accumulate)

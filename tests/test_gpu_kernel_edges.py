@@ -290,3 +290,56 @@ def test_selection_dot_team(case):
     torch.cuda.synchronize()
     assert torch.equal(idx, idx2) and torch.equal(g, g2)
     assert np.array_equal(y.cpu().numpy().view(np.uint8), y2.cpu().numpy().view(np.uint8))
+
+
+# (T, d, d_key, n_rows, n_cols, H): bf16 logits on 64 x 64, 128 x 64, 128 x 128 and 256 x 256 tiles: one k step, fewer than the
+# ring holds and more; tokens and keys at a tile's edge and past it, an uneven pair of halves.
+TILE_CASES = [(65, 128, 64, 64, 65, 1), (70, 256, 128, 3, 130, 2), (129, 1024, 512, 100, 7, 3), (200, 2048, 1024, 1024, 1000, 8),
+              (257, 256, 128, 512, 512, 8), (500, 512, 256, 1024, 1024, 8), (513, 128, 64, 700, 1025, 9),
+              (769, 128, 64, 2048, 2047, 4)]
+
+
+@pytest.mark.parametrize("case", TILE_CASES, ids=[str(c) for c in TILE_CASES])
+def test_bf16_logit_tiles(case):
+    T, d, dk, nr, nc, H = case
+    say(f"[bf16 logits] {case}")
+    w = synth.Workload("tiles", T=T, d=d, n_rows=nr, n_cols=nc, d_key=dk, H=H, K=1)
+    x, (kr, kc) = synth.make_x(w), synth.make_keys(w)
+    hs = torch.full((T, H, nr + nc), float("nan"), device="cuda")
+    idx = torch.empty((T, H, 1), dtype=torch.int32, device="cuda")
+    g = torch.empty((T, H, 1), device="cuda")
+    P.omnimoe_route(B.make_desc(w), to_dev(x), to_dev(kr), to_dev(kc), idx, g, half_scores=hs)
+    torch.cuda.synchronize()
+    hs = hs.cpu().numpy()
+    # Higham's bound on a sample of the tokens: the first, the last and those around each tile edge
+    rows = sorted({t for e in range(0, T + 256, 64) for t in (e - 1, e) if 0 <= t < T} | {T - 1})
+    fx, fr, fc = synth.as_f32(x)[rows], synth.as_f32(kr), synth.as_f32(kc)
+    for keys, xq, got in ((fr, fx[:, :dk], hs[rows][..., :nr]), (fc, fx[:, dk:2 * dk], hs[rows][..., nr:])):
+        ref = np.matmul(xq.astype(np.float64)[None], keys.astype(np.float64).transpose(0, 2, 1)).transpose(1, 0, 2)
+        bound = np.matmul(np.abs(xq).astype(np.float64)[None],
+                          np.abs(keys).astype(np.float64).transpose(0, 2, 1)).transpose(1, 0, 2)
+        gamma = dk * 2.0 ** -23 / (1 - dk * 2.0 ** -23)
+        assert np.all(np.abs(got - ref) <= 2 * gamma * bound + 1e-30)
+    assert np.isfinite(hs).all()
+
+
+# (T, d, d_ff): the accumulating projection on each tile, on top of what y holds
+MLP_TILE_CASES = [(66, 192, 64), (300, 704, 704), (700, 1024, 512), (1500, 512, 1024)]
+
+
+@pytest.mark.parametrize("case", MLP_TILE_CASES, ids=[str(c) for c in MLP_TILE_CASES])
+def test_shared_mlp_tiles(case):
+    T, d, d_ff = case
+    say(f"[shared mlp] {case}")
+    w = synth.Workload("mlpt", T=T, d=d, n_rows=2, n_cols=2, d_key=8, H=1, K=1)
+    x, (gu, dn) = synth.make_x(w), synth.make_mlp_weights(w, d_ff)
+    y0 = np.random.default_rng(3).standard_normal((T, d)).astype(np.float32)
+    y = to_dev(y0.copy())
+    P.omnimoe_shared_mlp(B.make_desc(w), d_ff, to_dev(x), to_dev(gu), to_dev(dn), y)
+    torch.cuda.synchronize()
+    fx, fg, fd = (synth.as_f32(v).astype(np.float64) for v in (x, gu, dn))
+    h = fx @ fg.T
+    act = h[:, :d_ff] / (1 + np.exp(-h[:, :d_ff])) * h[:, d_ff:]
+    # silu(g) u rounded to bf16 (2^-8 relative at most, with the fp32 products before it) times w_down
+    bound = (2.0 ** -8) * (np.abs(act) @ np.abs(fd).T) + 1e-5 * (np.abs(fx) @ np.abs(fg).T).max() + 1e-6
+    assert np.all(np.abs(y.cpu().numpy() - (y0 + act @ fd.T)) <= bound)
