@@ -483,8 +483,9 @@ __global__ __launch_bounds__(256) void select_kernel(SelectArgs a) {
 // One workgroup per (token, head) row, for K beyond one wavefront (eight waves when the final
 // order holds 2048 keys or more, four below, where more rows share a compute unit):
 //   1. each half is put in (logit desc, index asc) order: a half of at most 512 logits by a
-//      bitonic sort in one wave's registers (the two halves on two waves), a longer half by a
-//      bitonic sort in LDS;
+//      bitonic sort in the registers of two waves (512 keys on one wave each left two SIMDs of
+//      the compute unit with twice the others' instructions), a longer half by a bitonic
+//      sort in LDS;
 //   2. the K-th largest cell score s* of the grid of the top Kr rows and top Kc columns (the
 //      whole top K lies in it, see the file header). Row rank a holds the cells (a, b) in
 //      descending score as b grows, so the number of its cells scoring at least u is found by
@@ -498,14 +499,16 @@ __global__ __launch_bounds__(256) void select_kernel(SelectArgs a) {
 //   4. the selected cells of row rank a are then its first t_a columns: they are written out
 //      at the offsets of an exclusive scan of t_a, one run per row rank, each run already in
 //      the final order (score descending, id ascending);
-//   5. from 1024 keys on the runs are merged pairwise, level by level (merge path, in place);
-//      up to 512 keys a bitonic sort over LDS is faster;
+//   5. they are put in score buckets and each key is ranked among its bucket's; a row with a bucket
+//      that is too full merges the runs pairwise, level by level (merge path, in place), from 1024 keys
+//      on, and sorts up to 512 keys bitonically over LDS;
 //   6. gates: softmax over the K scores, summed in a fixed order.
 // Scores are compared as exact doubles (sums of two floats), integer keys elsewhere, so the
 // result is exact and independent of thread timing.
 
 constexpr int kLargeMaxWaves = 8;  // workgroups of 256 or 512 threads
 constexpr int kMergeMinKeys = 1024;  // final order by merging the runs from k2 = 1024 keys on
+constexpr int kBucketMax = 64;       // fullest score bucket that is ranked key by key
 
 struct LargeArgs {
   const float* hs;
@@ -578,51 +581,61 @@ __device__ __forceinline__ void block_sum3(LargeShared& sh, int (&v)[3], int w, 
   }
 }
 
-// Descending bitonic sort of 512 keys held by one wave, eight consecutive keys per lane
-// (key i = 8 lane + q in x[q]): partner distances below 8 are exchanges between a lane's own
-// registers, larger ones swap with lane l ^ (distance / 8) through DPP and the lane-half swaps.
+// Bitonic sort of 256 keys held by one wave, four consecutive keys per lane (key base + 4 lane + q
+// in x[q]), as one part of a descending sort of 512: base 0 ends descending, base 256 ascending.
+// Partner distances below 4 are exchanges between a lane's own registers, larger ones swap
+// with lane l ^ (distance / 4) through DPP and the lane-half swaps.
 template <int J>
-__device__ __forceinline__ void ce_lanes(uint64_t (&x)[8], int k) {
+__device__ __forceinline__ void ce_lanes(uint64_t (&x)[4], int base, int k) {
   const int l = lane_id();
   const bool lower = (l & J) == 0;
 #pragma unroll
-  for (int q = 0; q < 8; ++q) {
+  for (int q = 0; q < 4; ++q) {
     const uint64_t o = xor_lane64<J>(x[q]);
-    const bool desc = ((8 * l + q) & k) == 0;
+    const bool desc = ((base + 4 * l + q) & k) == 0;
     x[q] = (lower == desc) ? (x[q] > o ? x[q] : o) : (x[q] > o ? o : x[q]);
   }
 }
 
-__device__ __forceinline__ void wave_sort512_desc(uint64_t (&x)[8]) {
+// The exchanges of stage k at distances 2^lj_first .. 1.
+template <int LJ>
+__device__ __forceinline__ void ce_stage(uint64_t (&x)[4], int base, int k) {
   const int l = lane_id();
 #pragma unroll
-  for (int lk = 1; lk <= 9; ++lk) {
-    const int k = 1 << lk;
+  for (int lj = LJ; lj >= 0; --lj) {
+    const int j = 1 << lj;
+    if (j >= 4) {
+      switch (j >> 2) {
+        case 1: ce_lanes<1>(x, base, k); break;
+        case 2: ce_lanes<2>(x, base, k); break;
+        case 4: ce_lanes<4>(x, base, k); break;
+        case 8: ce_lanes<8>(x, base, k); break;
+        case 16: ce_lanes<16>(x, base, k); break;
+        default: ce_lanes<32>(x, base, k); break;
+      }
+    } else {
 #pragma unroll
-    for (int lj = lk - 1; lj >= 0; --lj) {
-      const int j = 1 << lj;
-      if (j >= 8) {
-        switch (j >> 3) {
-          case 1: ce_lanes<1>(x, k); break;
-          case 2: ce_lanes<2>(x, k); break;
-          case 4: ce_lanes<4>(x, k); break;
-          case 8: ce_lanes<8>(x, k); break;
-          case 16: ce_lanes<16>(x, k); break;
-          default: ce_lanes<32>(x, k); break;
-        }
-      } else {
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-          if (q & j) continue;
-          const bool desc = ((8 * l + q) & k) == 0;
-          const uint64_t p0 = x[q], p1 = x[q + j];
-          const bool swap = desc ? (p0 < p1) : (p0 > p1);
-          x[q] = swap ? p1 : p0;
-          x[q + j] = swap ? p0 : p1;
-        }
+      for (int q = 0; q < 4; ++q) {
+        if (q & j) continue;
+        const bool desc = ((base + 4 * l + q) & k) == 0;
+        const uint64_t p0 = x[q], p1 = x[q + j];
+        const bool swap = desc ? (p0 < p1) : (p0 > p1);
+        x[q] = swap ? p1 : p0;
+        x[q + j] = swap ? p0 : p1;
       }
     }
   }
+}
+
+__device__ __forceinline__ void wave_sort256(uint64_t (&x)[4], int base) {
+  ce_stage<0>(x, base, 2);
+  ce_stage<1>(x, base, 4);
+  ce_stage<2>(x, base, 8);
+  ce_stage<3>(x, base, 16);
+  ce_stage<4>(x, base, 32);
+  ce_stage<5>(x, base, 64);
+  ce_stage<6>(x, base, 128);
+  ce_stage<7>(x, base, 256);
 }
 
 // RPT: row ranks per thread in the searches (kr <= RPT * NT). MERGE: the final order by merging
@@ -650,24 +663,49 @@ __global__ __launch_bounds__(NT, NT == 256 ? 5 : 4) void select_large_kernel(Lar
 
   for (int64_t row = blockIdx.x; row < a.rows; row += gridDim.x) {
     const float* hr = a.hs + row * (int64_t)(a.nr + a.nc);
-    // 1. the top kr row keys and top kc column keys, descending. Halves of at most 512 logits:
-    // wave 0 sorts the rows and wave 1 the columns, each in its registers; longer halves: a
+    // 1. the top kr row keys and top kc column keys, descending. Halves of at most 512 logits: two
+    // waves per half, each 256 in its registers (so on all four SIMDs); longer halves: a
     // bitonic sort in LDS by the whole workgroup. Keys are padded with 0 (below every finite
     // logit).
     if (n2 <= 512) {
-      if (w < 2) {
-        const int n = w == 0 ? a.nr : a.nc;
-        const float* src = hr + (w == 0 ? 0 : a.nr);
-        uint64_t x[8];
+      // wave w < 4: keys 256 (w % 2) .. + 255 of half w / 2 (waves 0 and 2 alone up to 256 logits)
+      const int half = w >> 1, base = (w & 1) * 256;
+      const bool sorts = w < 4 && base < n2;
+      uint64_t x[4];
+      if (sorts) {
+        const int n = half ? a.nc : a.nr;
+        const float* src = hr + half * a.nr;
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
-          const int j = 8 * l + q;
+        for (int q = 0; q < 4; ++q) {
+          const int j = base + 4 * l + q;
           x[q] = j < n ? logit_key(ord_f32(src[j]), j) : 0ull;
         }
-        wave_sort512_desc(x);
+        wave_sort256(x, base);
+      }
+      uint64_t* const mine = hk + half * n2 + base + 4 * l;
+      if (n2 == 512) {
+        // the two parts form one bitonic sequence: the larger of each pair to the first part, the
+        // rest inside the waves
+        if (sorts) {
 #pragma unroll
-        for (int q = 0; q < 8; ++q)
-          if (8 * l + q < n2) hk[w * n2 + 8 * l + q] = x[q];
+          for (int q = 0; q < 4; ++q) mine[q] = x[q];
+        }
+        __syncthreads();
+        if (sorts) {
+          const uint64_t* const other = hk + half * n2 + (256 - base) + 4 * l;
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const uint64_t o = other[q];
+            x[q] = (base == 0) == (x[q] > o) ? x[q] : o;
+          }
+          ce_stage<7>(x, 0, 512);
+        }
+        __syncthreads();
+      }
+      if (sorts) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (base + 4 * l + q < n2) mine[q] = x[q];
       }
       __syncthreads();
     } else {
@@ -895,7 +933,127 @@ __global__ __launch_bounds__(NT, NT == 256 ? 5 : 4) void select_large_kernel(Lar
     // the merge path, the rest from a sequential merge with the two heads in registers (moving
     // on to the next run where one ends); after a barrier the outputs are written in place.
     // Keys are unique (distinct ids), so the order is fully determined.
-    if constexpr (!MERGE) {
+    // By buckets of score first: bucket b = floor((S_0 - S) scale) of nb (the rounded difference and
+    // product fall as S rises, so an earlier bucket holds no lower score, and equal scores share one);
+    // counts by LDS atomics, a scan, every key to any place of its bucket, and then each key's rank among
+    // the few of its bucket gives its final place. The atomics' order only moves keys inside
+    // a bucket, so the result does not depend on it. A row whose fullest bucket holds more than
+    // kBucketMax keys (ties, far outliers) is ordered by the runs below instead. It takes two passes of the
+    // keys through LDS and about a bucket's keys per key, against one pass per merge level or sort
+    // stage: selection of 4096 rows of the 320 x 320 grid, K = 4096 581 -> 492 us, K = 512 183 -> 163
+    // (with the half sorts on four waves 457 and 155).
+    bool ordered = false;
+    {
+      constexpr int kPer = MERGE ? (NT == 512 ? 8 : 4) : 2;  // keys per thread: NT kPer >= k2 >= K
+      int* cnt = (int*)smem;  // [nb]: the sorted halves are no longer needed
+      const int nb = 4 * n2 < 2048 ? 4 * n2 : 2048;
+      for (int i = tid; i < nb; i += kLargeThreads) cnt[i] = 0;
+      // S_0 is row rank 0's first cell; the last selected cell of every row rank bounds S from below
+      const double smax = f64_from_ord(sel_s[0]);
+      double smin = smax;
+      for (int r = tid; r < kr; r += kLargeThreads)
+        if (cnt_lo[r] > 0) {
+          const double v = f64_from_ord(sel_s[cnt_hi[r] + cnt_lo[r] - 1]);
+          smin = v < smin ? v : smin;
+        }
+      uint64_t lowest = ~ord_f64(smin);  // (largest complement: smallest score)
+      lowest = max_u64(lowest, xor_lane64<32>(lowest));
+      lowest = max_u64(lowest, xor_lane64<16>(lowest));
+      lowest = max_u64(lowest, xor_lane64<8>(lowest));
+      lowest = max_u64(lowest, xor_lane64<4>(lowest));
+      lowest = max_u64(lowest, xor_lane64<2>(lowest));
+      lowest = max_u64(lowest, xor_lane64<1>(lowest));
+      if (l == 0) sh.wmax[w] = lowest;
+      __syncthreads();
+#pragma unroll
+      for (int ww = 0; ww < kLargeWaves; ++ww) lowest = sh.wmax[ww] > lowest ? sh.wmax[ww] : lowest;
+      const double range = smax - f64_from_ord(~lowest);
+      const double scale = range > 0.0 ? (double)nb / range : 0.0;
+      auto bucket_of = [&](uint64_t key) {
+        const double d = (smax - f64_from_ord(key)) * scale;
+        return d < (double)(nb - 1) ? (int)d : nb - 1;
+      };
+      uint64_t es[kPer];
+      uint32_t en[kPer];
+      int ep[kPer];  // bucket and place in it, later the final place
+#pragma unroll
+      for (int q = 0; q < kPer; ++q) {
+        const int i = tid + q * kLargeThreads;
+        if (i < K) {
+          es[q] = sel_s[i];
+          en[q] = sel_n[i];
+          const int b = bucket_of(es[q]);
+          ep[q] = (atomicAdd(&cnt[b], 1) << 16) | b;
+        }
+      }
+      __syncthreads();
+      // exclusive scan of the counts (each thread a contiguous piece) and the fullest bucket
+      const int per = (nb + kLargeThreads - 1) / kLargeThreads, b0 = tid * per;
+      int loc = 0, full = 0;
+      for (int b = b0; b < b0 + per && b < nb; ++b) {
+        loc += cnt[b];
+        full = cnt[b] > full ? cnt[b] : full;
+      }
+      const int ex = wave_excl_scan_i32(loc);
+      const uint64_t over = __ballot(full > kBucketMax);
+      if (l == kWave - 1) sh.wint[w] = ex + loc;
+      if (l == 0) sh.cnt[0][0][w] = over != 0ull;
+      __syncthreads();
+      int run = ex, bad = 0;
+      for (int ww = 0; ww < kLargeWaves; ++ww) {
+        if (ww < w) run += sh.wint[ww];
+        bad |= sh.cnt[0][0][ww];
+      }
+      if (!bad) {
+        for (int b = b0; b < b0 + per && b < nb; ++b) {
+          const int c = cnt[b];
+          cnt[b] = run;
+          run += c;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < kPer; ++q)
+          if (tid + q * kLargeThreads < K) {
+            const int at = cnt[ep[q] & 0xFFFF] + (ep[q] >> 16);
+            sel_s[at] = es[q];
+            sel_n[at] = en[q];
+          }
+        __syncthreads();
+        // (the keys by place, so that neighbouring lanes read the same buckets)
+#pragma unroll
+        for (int q = 0; q < kPer; ++q) {
+          const int i = tid + q * kLargeThreads;
+          if (i < K) {
+            const uint64_t me = sel_s[i];
+            const uint32_t mn = sel_n[i];
+            const int b = bucket_of(me);
+            int at = cnt[b];
+            const int hi2 = b + 1 < nb ? cnt[b + 1] : K;
+            for (int j = at; j < hi2; ++j) {
+              const uint64_t o = sel_s[j];
+              bool first = o > me;
+              if (o == me) first = sel_n[j] > mn;
+              at += first;
+            }
+            es[q] = me;
+            en[q] = mn;
+            ep[q] = at;
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < kPer; ++q)
+          if (tid + q * kLargeThreads < K) {
+            sel_s[ep[q]] = es[q];
+            sel_n[ep[q]] = en[q];
+          }
+        ordered = true;
+      }
+      __syncthreads();
+    }
+    if (ordered) {
+    } else if constexpr (!MERGE) {
       // short lists (k2 <= 512): a bitonic sort over LDS (keys past K padded with 0, below
       // every key) takes fewer cycles than the merge levels (at K = 512: 25k against 31k)
       for (int i = K + tid; i < k2; i += kLargeThreads) {

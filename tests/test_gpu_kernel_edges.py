@@ -7,7 +7,7 @@ import pytest
 
 import oracle
 import synth
-from gpu_support import backward_error_bounds, grouped_gap_bound, higham_bound, to_dev, upload
+from gpu_support import GATE_TOL, backward_error_bounds, grouped_gap_bound, higham_bound, to_dev, upload
 
 pytestmark = pytest.mark.gpu
 
@@ -343,3 +343,34 @@ def test_shared_mlp_tiles(case):
     # silu(g) u rounded to bf16 (2^-8 relative at most, with the fp32 products before it) times w_down
     bound = (2.0 ** -8) * (np.abs(act) @ np.abs(fd).T) + 1e-5 * (np.abs(fx) @ np.abs(fg).T).max() + 1e-6
     assert np.all(np.abs(y.cpu().numpy() - (y0 + act @ fd.T)) <= bound)
+
+
+# (n_rows, n_cols, K, kind): more than 64 picks per row: halves of one and two sorting waves at their edges; the order by score
+# buckets and, where a bucket is too full (coarse scores, one far outlier, every score alike), by merged runs or a sort.
+LARGE_K_CASES = [(256, 257, 512, "normal"), (512, 512, 513, "normal"), (300, 100, 65, "normal"), (513, 40, 700, "normal"),
+                 (320, 320, 2048, "normal"), (17, 16, 200, "normal"), (320, 320, 4096, "coarse"),
+                 (512, 256, 400, "coarse"), (320, 320, 1024, "outlier"), (64, 80, 300, "outlier"),
+                 (320, 320, 512, "alike"), (256, 256, 3000, "alike"), (512, 511, 4096, "mixed")]
+
+
+@pytest.mark.parametrize("case", LARGE_K_CASES, ids=[str(c) for c in LARGE_K_CASES])
+def test_select_large_orders(case):
+    nr, nc, K, kind = case
+    say(f"[select] {case}")
+    rng = np.random.default_rng(nr + nc + K)
+    T = 7
+    hs = rng.standard_normal((T, 1, nr + nc)).astype(np.float32)
+    if kind in ("coarse", "mixed"):
+        hs[::2 if kind == "mixed" else 1] = np.round(hs[::2 if kind == "mixed" else 1] * 4) / 4
+    if kind == "outlier":
+        hs[:, 0, 3], hs[:, 0, nr + 5] = 64.0, 100.0  # (sums stay exact in double)
+    if kind == "alike":
+        hs[:] = 0.25
+    w = synth.Workload("sel", T=T, d=16, n_rows=nr, n_cols=nc, d_key=8, H=1, K=K, dtype="f32")
+    idx = torch.empty((T, 1, K), dtype=torch.int32, device="cuda")
+    g = torch.empty((T, 1, K), dtype=torch.float32, device="cuda")
+    P.omnimoe_select(B.make_desc(w), to_dev(hs), idx, g)
+    torch.cuda.synchronize()
+    ri, _, rg, inexact = oracle.select_f32(oracle.desc(w), hs, oracle.BRUTE)
+    assert inexact == 0 and np.array_equal(idx.cpu().numpy(), ri)
+    np.testing.assert_allclose(g.cpu().numpy(), rg, rtol=GATE_TOL, atol=1e-7)
