@@ -203,8 +203,8 @@ __device__ __forceinline__ int swz(int r) { return (r >> 1) & 7; }
 
 __device__ __forceinline__ void wait_vm0() { __builtin_amdgcn_s_waitcnt(0x0F70); }  // vmcnt(0)
 template <int N>
-__device__ __forceinline__ void wait_vm() {  // vmcnt(N)
-  __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
+__device__ __forceinline__ void wait_vm_lds() {  // vmcnt(N) and lgkmcnt(0)
+  __builtin_amdgcn_s_waitcnt(0x0070 | (N & 15) | ((N >> 4) << 14));
 }
 
 // Epilogue of the masked-activation product (the first product of Eq. 14 over all experts).
@@ -551,9 +551,10 @@ __global__ __launch_bounds__(256, 2) void score_bf16_mid_kernel(ScoreArgs a) {
     if (s < KT) issue(s, s * LK);
   int stage = 0;
   for (int kt = 0; kt < KT; ++kt) {
-    // copies of the NS - 2 later steps may still be in flight
-    if (kt + NS - 1 <= KT) wait_vm<(NS - 2) * (LA + LB)>();
-    else wait_vm0();
+    // copies of the NS - 2 later steps may still be in flight; the wave's own reads of the stage before
+    // are done, so that the copies issued after the barrier cannot overtake them
+    if (kt + NS - 1 <= KT) wait_vm_lds<(NS - 2) * (LA + LB)>();
+    else wait_vm_lds<0>();
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");

@@ -149,7 +149,7 @@ __global__ __launch_bounds__(64 * NW, 8) void sweep_sum_kernel(SweepArgs a) {
       const int2 cur = ent;
       const int nx = base + 16 + (l & 15);
       ent = L[nx < a.hk ? nx : a.hk - 1];
-      const int w0 = base + (l & 15) < a.hk ? cur.y : 0;  // entries past the end add nothing
+      const int left = a.hk - base;
       uint4 r[G];
       sixteen<G>(
           [&](auto J) {
@@ -158,7 +158,8 @@ __global__ __launch_bounds__(64 * NW, 8) void sweep_sum_kernel(SweepArgs a) {
           },
           [&](auto J) {
             constexpr int j = decltype(J)::value;
-            const float w = __int_as_float(row_bcast<j>(w0));
+            if (j >= left) return;  // past the end: loaded again, not added
+            const float w = __int_as_float(row_bcast<j>(cur.y));
             const uint4 c = r[j % G];
             if constexpr (BF16) {
               acc[0] = fmaf(w, bf16_lo(c.x), acc[0]);

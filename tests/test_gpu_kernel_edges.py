@@ -258,6 +258,30 @@ def test_sweep_layer(case):
     assert np.array_equal(ys[0].view(np.uint8), ys[1].view(np.uint8))
 
 
+# (T, H, K): slots that sixteen does not divide; the loads past a token's last task repeat a row that must not be added again
+SWEEP_TAIL_CASES = [(512, 2, 7), (520, 3, 13), (2048, 2, 9)]
+
+
+@pytest.mark.parametrize("case", SWEEP_TAIL_CASES, ids=[str(c) for c in SWEEP_TAIL_CASES])
+def test_sweep_tail_adds_nothing(case):
+    T, H, K = case
+    say(f"[sweep tail] {case}")
+    w = synth.Workload("tail", T=T, d=1024, n_rows=7, n_cols=9, d_key=16, H=H, K=K)
+    dev, D = upload(synth.make_inputs(w)), B.make_desc(w)
+    # an overflowed value of every expert in a column of its own: the sum there is infinite where the token picked that
+    # expert and finite elsewhere (zero times such a row would be NaN)
+    e = torch.arange(w.N, device="cuda")
+    dev["v"].view(torch.bfloat16)[e, e] = float("inf")
+    y = torch.full((T, 1024), float("nan"), device="cuda")
+    idx = torch.empty((T, H, K), dtype=torch.int32, device="cuda")
+    g = torch.empty((T, H, K), device="cuda")
+    P.omnimoe_layer_forward(D, dev["x"], dev["keys_row"], dev["keys_col"], dev["u"], dev["v"], y, idx, g)
+    torch.cuda.synchronize()
+    picked = torch.zeros((T, 1024), dtype=torch.bool, device="cuda").scatter_(1, idx.view(T, -1).long(), True)
+    assert not torch.isnan(y).any()
+    assert torch.equal(torch.isinf(y), picked)
+
+
 # (T, n, d, H, K): the selection that forms the dot with a workgroup per row (up to 512 rows) and with a wave per row past it; picks
 # that four waves share evenly, unevenly, and fewer picks than waves.
 TEAM_CASES = [(64, 256, 512, 4, 16), (512, 256, 512, 1, 13), (513, 256, 512, 1, 13), (128, 512, 1024, 3, 64),
