@@ -496,8 +496,13 @@ omnimoe_status omnimoe_shared_mlp(const omnimoe_layer_desc* desc, int32_t d_ff, 
   g.nc = 0;
   g.dk = s.d;
   g.col0 = 0;
-  hipError_t e = omnimoe::launch_score(g, x, w_gu, w_gu, h, strm);
-  if (e == hipSuccess) e = omnimoe::launch_swiglu(s.T, d_ff, s.bf16, h, act, strm);
+  hipError_t e;
+  if (omnimoe::gate_up_fusable(s, d_ff)) {
+    e = omnimoe::launch_gate_up(s, d_ff, x, w_gu, h, act, strm);
+  } else {
+    e = omnimoe::launch_score(g, x, w_gu, w_gu, h, strm);
+    if (e == hipSuccess) e = omnimoe::launch_swiglu(s.T, d_ff, s.bf16, h, act, strm);
+  }
   // down projection added into y: y [T, d] += act w_down^T
   Shape dn = s;
   dn.H = 1;

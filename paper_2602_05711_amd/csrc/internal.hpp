@@ -30,6 +30,13 @@ hipError_t launch_score(const Shape& s, const void* x, const void* keys_row,
                         const void* keys_col, float* half_scores, hipStream_t st,
                         bool accumulate = false);
 
+// Both projections of the shared branch and the step between them in one kernel, a[t, f] = silu(x_t . g_f) (x_t . u_f) in
+// bf16, where gate_up_fusable: the same products in the same order as launch_score and launch_swiglu, without
+// the fp32 rows in memory. sink: workspace of at least 4 bytes (the prefetch's).
+bool gate_up_fusable(const Shape& s, int d_ff);
+hipError_t launch_gate_up(const Shape& s, int d_ff, const void* x, const void* w_gu, void* sink,
+                          void* act, hipStream_t st);
+
 // a[t, f] = silu(h[t, f]) * h[t, d_ff + f] for h [T, 2 d_ff] fp32; a [T, d_ff] in the layer's
 // dtype (bf16 by round-to-nearest-even).
 hipError_t launch_swiglu(int64_t T, int d_ff, bool bf16, const float* h, void* a,

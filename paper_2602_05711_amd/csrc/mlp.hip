@@ -1,7 +1,8 @@
 // The shared dense branch MLP(x) of Eq. 7 as a SwiGLU block: two projections run on the logit
 // GEMM kernels (gate and up rows in one GEMM into an fp32 buffer, then the down projection
 // added into y), and this elementwise step between them: a = silu(g) * u, stored in the
-// layer's dtype so that the down projection runs on MFMA for bf16.
+// layer's dtype so that the down projection runs on MFMA for bf16. Where the gate and up GEMM has
+// enough tiles its epilogue takes this step itself (launch_gate_up).
 #include "device_common.hpp"
 #include "internal.hpp"
 

@@ -347,8 +347,10 @@ def test_bf16_logit_tiles(case):
     assert np.isfinite(hs).all()
 
 
-# (T, d, d_ff): the accumulating projection on each tile, on top of what y holds
-MLP_TILE_CASES = [(66, 192, 64), (300, 704, 704), (700, 1024, 512), (1500, 512, 1024)]
+# (T, d, d_ff): the accumulating projection on each tile, on top of what y holds; the gate and up projections with the step
+# between them in one kernel on 128 x 128 and 256 x 256 tiles, features and tokens past a tile's edge
+MLP_TILE_CASES = [(66, 192, 64), (300, 704, 704), (700, 1024, 512), (1500, 512, 1024), (1501, 128, 2056),
+                  (3001, 64, 2056), (3072, 192, 2048), (65, 64, 16384)]
 
 
 @pytest.mark.parametrize("case", MLP_TILE_CASES, ids=[str(c) for c in MLP_TILE_CASES])
