@@ -267,8 +267,9 @@ omnimoe_status omnimoe_expert_forward_token_centric(const omnimoe_layer_desc* de
  *                               gradient of the K selected scores through the softmax (Eq. 2)
  * x, u, v, idx, gates as in omnimoe_expert_forward; dy [T, d] fp32; perm, active_offsets and
  * n_active from omnimoe_schedule with group_size 1 (each expert's tasks contiguous). The
- * per-expert sums run over the schedule's segments in task order, so the result is the same
- * on every run. d <= 4096 (bf16) or 2048 (fp32), else OMNIMOE_ERR_UNSUPPORTED. Workspace:
+ * per-expert sums run over the schedule's segments in task order (a segment of more than 16
+ * tasks, or M / 2048 where that is more, in pieces whose sums are added in order), so the
+ * result is the same on every run. d <= 4096 (bf16) or 2048 (fp32), else OMNIMOE_ERR_UNSUPPORTED. Workspace:
  * OMNIMOE_STAGE_EXPERT_BACKWARD bytes. */
 omnimoe_status omnimoe_expert_backward(const omnimoe_layer_desc* desc, const void* x,
                                        const void* u, const void* v, const int32_t* idx,

@@ -191,7 +191,7 @@ size_t stage_bytes(const Shape& s, int stage) {
     case OMNIMOE_STAGE_SCHEDULE: return omnimoe::schedule_ws_bytes(s.M, s.N);
     case OMNIMOE_STAGE_EXPERT: return m_bytes(s) + omnimoe::dense_accumulate_ws_bytes(s);
     case OMNIMOE_STAGE_ROUTE_DENSE: return dense_bytes(s);
-    case OMNIMOE_STAGE_EXPERT_BACKWARD: return omnimoe::backward_ws_bytes(s.M);
+    case OMNIMOE_STAGE_EXPERT_BACKWARD: return omnimoe::backward_ws_bytes(s);
     case OMNIMOE_STAGE_ROUTE_BACKWARD: return omnimoe::route_backward_ws_bytes(s);
     case OMNIMOE_STAGE_EXPERT_SCATTER: return m_bytes(s) + align_up((size_t)s.M * s.d * 4);
     case OMNIMOE_STAGE_EXPERT_GROUP_ROWS: {

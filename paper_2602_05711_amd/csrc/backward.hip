@@ -8,9 +8,10 @@
 // expert pass: one wavefront walks the segments of one or two active experts (task ids
 //   ascending), forms h, da, a, dh and dgates of every task and sums du and dv in that order: the
 //   expert-major order makes the per-expert gradients plain sequential sums, with no atomics, so
-//   every run gives the same bits;
+//   every run gives the same bits; a segment of more than piece_tasks(M) tasks is cut at the
+//   multiples of that number, its pieces go to waves of their own, and their sums are added in order;
 // dx: the forward's token-major routed sum with dh in the place of a and u in the place of v;
-// score pass: one wavefront per (token, head) row.
+// score pass: one wavefront per (token, head) row; the same launch adds the pieces' sums to du and dv.
 // Router backward (selections fixed; S_p = s_r[i_p] + s_c[j_p]): the tasks of a (token, head) row
 // that share a sub-key are merged into one pick, the picks of both halves are put in sub-key order
 // by one counting pass, and one wavefront per sub-key sums its picks' w x_t, tokens ascending; the input
@@ -41,6 +42,8 @@ struct BwdArgs {
   float* dgates;
   float* dscores;
   float* dh;   // dh_p per task (workspace)
+  int32_t* piece_row;  // [blocks] du / dv row that the piece from position j << piece_bits on belongs to, or -1
+  float* piece_sum;    // [blocks][2][d] its du and dv
   int64_t T;
   int64_t N;
   int64_t M;
@@ -50,6 +53,10 @@ struct BwdArgs {
   int K;
   int act;
   int run;      // consecutive active experts per wave (at most 63)
+  int piece_bits;  // log2 of the tasks of a piece
+  int blocks;      // ceil(M / piece): positions where a piece may begin
+  int piece_wgs;   // workgroups of the expert pass that look for pieces (a multiple of 8)
+  int score_wgs;   // workgroups of the score pass that take rows
 };
 
 __device__ __forceinline__ int clamp_id(int v, int64_t n) {
@@ -113,6 +120,25 @@ struct Quad<false> {
   }
 };
 
+__device__ __forceinline__ int clamp_pos(int v, int64_t m) {
+  return v < 0 ? 0 : (v > m ? (int)m : v);
+}
+
+// The last of n ascending segment starts that is at most pos (the first where none is): the wave
+// probes 64 of them at a time.
+__device__ __forceinline__ int64_t segment_of(const int32_t* offsets, int64_t n, int pos) {
+  int64_t lo = 0, hi = n;
+  while (hi - lo > 1) {
+    const int64_t step = (hi - lo + kWave - 1) / kWave;
+    const int64_t q = lo + lane_id() * step;
+    const uint64_t m = __ballot(q < hi && offsets[q < hi ? q : lo] <= pos);
+    const int c = __popcll(m);
+    lo += (c > 0 ? c - 1 : 0) * step;
+    hi = lo + step < hi ? lo + step : hi;
+  }
+  return lo;
+}
+
 // Expert pass: a wave takes a.run consecutive active experts. It reads the run's segment bounds
 // and then the segments' tasks, experts and gates 64 positions at a time with one load per lane.
 // Per expert it loads u_e and v_e once and takes the tasks G at a time with all of their token and
@@ -132,6 +158,16 @@ struct Quad<false> {
 // and the routed sum 7.02 ms (two experts per wave; four 7.03, eight 7.32; two tasks in flight instead of
 // one 7.49; four waves sharing an expert's columns 7.27); 4093 tokens, 2^16 experts of d = 512: 236 ->
 // 156 us (G = 4; 161 with two in flight, 169 with six).
+//
+// A wave forms about one task a microsecond, so an expert that many tokens pick would be walked by one wave
+// while the chip idles. A segment of more than one piece of tasks (16, or M / 2048 where that is more: at most
+// about 2048 pieces, the waves that the chip holds at d = 2048, and as many rows of workspace) is cut at the
+// multiples of a piece: its expert's wave takes the tasks up to the first cut, and the first a.piece_wgs
+// workgroups the other pieces, one a wave, with sums of their own that bwd_score_kernel's launch adds in order.
+// Zipf-distributed picks (exponent, tasks of the most picked expert), before and after: training shape, 0.6
+// (3278) 8990 -> 8200 us, 0.8 (27473) 36310 -> 7756, 1.0 (145305) 159.1 -> 6.6 ms; 4096 tokens, 2^16 experts of d =
+// 512, 0.6 (1248) 674 -> 231 us, 1.0 (22585) 8979 -> 205; 300 tokens of 8 tasks, 900 experts of d = 64, 0.6 (63)
+// 33 -> 17. Looking for pieces where there is none costs up to 1 us (uniform picks: 198 and 198 us, 16.0 and 16.6).
 template <int CPL, bool BF16, bool FULL, int G, bool NTL>
 __global__ __launch_bounds__(256) void bwd_expert_kernel(BwdArgs a) {
   typedef Quad<BF16> Q;
@@ -142,24 +178,48 @@ __global__ __launch_bounds__(256) void bwd_expert_kernel(BwdArgs a) {
 #pragma unroll
   for (int q = 0; q < CPL; ++q) cv[q] = FULL || (l + kWave * q) < rc;
   const int64_t na = *a.n_active < a.cap ? *a.n_active : a.cap;
-  // the grid covers a.cap experts; the workgroups that the active ones need are shared out to the
-  // XCDs (workgroup b runs on XCD b % 8) in contiguous parts
-  const int64_t nblk = (na + 4 * a.run - 1) / (4 * a.run);
-  if (blockIdx.x >= nblk) return;
-  const int64_t per_xcd = nblk / 8, extra = nblk % 8, xcd = blockIdx.x % 8;
-  const int64_t blk = xcd * per_xcd + (xcd < extra ? xcd : extra) + blockIdx.x / 8;
-  const int64_t r0 = (blk * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) * a.run;
-  if (r0 >= na) return;
-  const int n = (int)(na - r0 < a.run ? na - r0 : a.run);
-  int off = a.offsets[r0 + (l < n ? l : n)];
-  off = off < 0 ? 0 : (off > a.M ? (int)a.M : off);
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int piece = 1 << a.piece_bits;
+  int n, off;
+  f32x4_t *ou, *ov;  // the first segment's du and dv
+  if ((int)blockIdx.x < a.piece_wgs) {
+    // the piece that begins at position j * piece, if a segment of more tasks runs across it
+    const int j = (int)blockIdx.x * 4 + wv;
+    if (j >= a.blocks) return;
+    const int pos = j << a.piece_bits;
+    const int64_t r = na > 0 ? segment_of(a.offsets, na, pos) : 0;
+    const int b = clamp_pos(a.offsets[r], a.M), e = clamp_pos(a.offsets[r + 1], a.M);
+    const bool mine = na > 0 && b < pos && pos < e && e - b > piece;
+    if (l == 0) a.piece_row[j] = mine ? (int)r : -1;
+    if (!mine) return;
+    n = 1;
+    off = l == 0 ? pos : (e - pos < piece ? e : pos + piece);
+    ou = (f32x4_t*)a.piece_sum + (int64_t)j * 2 * rc;
+    ov = ou + rc;
+  } else {
+    // the grid covers a.cap experts; the workgroups that the active ones need are shared out to the
+    // XCDs (workgroup b runs on XCD b % 8) in contiguous parts
+    const int64_t wg = blockIdx.x - a.piece_wgs;
+    const int64_t nblk = (na + 4 * a.run - 1) / (4 * a.run);
+    if (wg >= nblk) return;
+    const int64_t per_xcd = nblk / 8, extra = nblk % 8, xcd = wg % 8;
+    const int64_t blk = xcd * per_xcd + (xcd < extra ? xcd : extra) + wg / 8;
+    const int64_t r0 = (blk * 4 + wv) * a.run;
+    if (r0 >= na) return;
+    n = (int)(na - r0 < a.run ? na - r0 : a.run);
+    off = clamp_pos(a.offsets[r0 + (l < n ? l : n)], a.M);
+    ou = (f32x4_t*)a.du + r0 * rc;
+    ov = (f32x4_t*)a.dv + r0 * rc;
+  }
   const int hk_shift = (a.hk & (a.hk - 1)) == 0 ? __builtin_ctz((unsigned)a.hk) : -1;
   auto token_of = [&](int p) { return hk_shift >= 0 ? p >> hk_shift : p / a.hk; };
   const int last = readlane_i32(off, n);  // end of the wave's positions
   TaskWindow w;
   w.base = -1;
   for (int i = 0; i < n; ++i) {
-    const int b = readlane_i32(off, i), e = readlane_i32(off, i + 1);
+    const int b = readlane_i32(off, i);
+    int e = readlane_i32(off, i + 1);
+    if (e - b > piece) e = ((b >> a.piece_bits) + 1) << a.piece_bits;  // its first piece
     f32x4_t du[CPL], dv[CPL];
 #pragma unroll
     for (int q = 0; q < CPL; ++q) du[q] = dv[q] = f32x4_t{0.f, 0.f, 0.f, 0.f};
@@ -248,21 +308,62 @@ __global__ __launch_bounds__(256) void bwd_expert_kernel(BwdArgs a) {
       }
       pos += cnt;
     }
-    f32x4_t* ou = (f32x4_t*)a.du + (r0 + i) * rc + l;
-    f32x4_t* ov = (f32x4_t*)a.dv + (r0 + i) * rc + l;
+    f32x4_t* const pu = ou + i * rc + l;
+    f32x4_t* const pv = ov + i * rc + l;
 #pragma unroll
     for (int q = 0; q < CPL; ++q) {
       if (!cv[q]) continue;
-      __builtin_nontemporal_store(du[q], ou + kWave * q);
-      __builtin_nontemporal_store(dv[q], ov + kWave * q);
+      __builtin_nontemporal_store(du[q], pu + kWave * q);
+      __builtin_nontemporal_store(dv[q], pv + kWave * q);
     }
   }
 }
 
+// Piece positions per workgroup of add_pieces.
+constexpr int kPieceGroup = 16;
+
+// du and dv of the rows whose segments were cut: the first piece's sum (in place) plus the others', in
+// order. Workgroup g takes 1024 columns of du or dv for the rows whose second piece is among kPieceGroup
+// positions.
+__device__ __forceinline__ void add_pieces(const BwdArgs& a, int g) {
+  const int slices = (a.d + 1023) / 1024;
+  const int64_t rc = a.d / 4;
+  const int which = g % 2, c = (g / 2) % slices * 256 + (int)threadIdx.x, j0 = g / (2 * slices) * kPieceGroup;
+  // lane i holds position j0 - 1 + i: a second piece is one whose predecessor belongs to another row
+  const int l = lane_id(), jl = j0 - 1 + l;
+  const int mine = l <= kPieceGroup && jl >= 0 && jl < a.blocks ? a.piece_row[jl] : -1;
+  const int before = __shfl_up(mine, 1, kWave);
+  for (uint64_t m = __ballot(l > 0 && mine >= 0 && mine != before); m; m &= m - 1) {
+    const int i = __builtin_ctzll(m), j = j0 - 1 + i;
+    const int64_t r = readlane_i32(mine, i);
+    if (c >= rc) continue;
+    const int e = clamp_pos(a.offsets[r + 1], a.M);
+    const int jend = (int)(((int64_t)e + (1 << a.piece_bits) - 1) >> a.piece_bits);
+    f32x4_t* const row = (f32x4_t*)(which ? a.dv : a.du) + r * rc + c;
+    const f32x4_t* const part = (const f32x4_t*)a.piece_sum + which * rc + c;
+    f32x4_t acc = *row;
+    constexpr int G = 8;
+    for (int k0 = j; k0 < jend; k0 += G) {
+      f32x4_t p[G];
+#pragma unroll
+      for (int k = 0; k < G; ++k)
+        p[k] = part[(int64_t)(k0 + k < jend ? k0 + k : jend - 1) * 2 * rc];
+#pragma unroll
+      for (int k = 0; k < G; ++k)
+        if (k0 + k < jend) acc += p[k];
+    }
+    *row = acc;
+  }
+}
+
 __global__ __launch_bounds__(256) void bwd_score_kernel(BwdArgs a) {
+  if ((int)blockIdx.x >= a.score_wgs) {
+    add_pieces(a, (int)blockIdx.x - a.score_wgs);
+    return;
+  }
   const int l = lane_id();
   const int64_t rows = a.T * (a.hk / a.K);
-  const int64_t stride = (int64_t)gridDim.x * 4;
+  const int64_t stride = (int64_t)a.score_wgs * 4;
   for (int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); row < rows; row += stride) {
     const int64_t base = row * a.K;
     float part = 0.0f;
@@ -564,7 +665,7 @@ constexpr int64_t kMallTableBytes = 128ll << 20;
 
 template <bool BF16, int CPL, int G>
 void launch_bwd(hipStream_t st, const BwdArgs& a) {
-  const dim3 grid((unsigned)((a.cap + 4 * a.run - 1) / (4 * a.run)));
+  const dim3 grid((unsigned)(a.piece_wgs + (a.cap + 4 * a.run - 1) / (4 * a.run)));
   const bool full = a.d == CPL * 4 * kWave;
   const bool ntl = a.N * (int64_t)a.d * (BF16 ? 2 : 4) > kMallTableBytes;
 #define OMNIMOE_BWD(F_, N_) \
@@ -592,7 +693,25 @@ hipError_t dispatch_bwd(int cpl, hipStream_t st, const BwdArgs& a) {
 
 }  // namespace
 
-size_t backward_ws_bytes(int64_t M) { return ((size_t)M * 4 + 255) & ~(size_t)255; }
+namespace {
+
+size_t al256(size_t v) { return (v + 255) & ~(size_t)255; }
+
+// log2 of the tasks of a piece (see bwd_expert_kernel): at least 16, and at most 2048 pieces, the waves that
+// the chip holds at the longest rows.
+int piece_bits(int64_t M) {
+  int b = 4;
+  while ((M >> b) > 2048) ++b;
+  return b;
+}
+int64_t piece_blocks(int64_t M) { return (M + (1ll << piece_bits(M)) - 1) >> piece_bits(M); }
+
+}  // namespace
+
+size_t backward_ws_bytes(const Shape& s) {
+  const size_t n = (size_t)piece_blocks(s.M);
+  return al256((size_t)s.M * 4) + al256(n * 4) + al256(n * 2 * s.d * 4);
+}
 
 hipError_t launch_expert_backward(const Shape& s, const void* x, const void* u, const void* v,
                                   const int32_t* idx, const float* gates, const int32_t* perm,
@@ -616,6 +735,11 @@ hipError_t launch_expert_backward(const Shape& s, const void* x, const void* u, 
   a.dgates = dgates;
   a.dscores = dscores;
   a.dh = (float*)ws;
+  a.piece_bits = piece_bits(s.M);
+  a.blocks = (int)piece_blocks(s.M);
+  a.piece_row = (int32_t*)((char*)ws + al256((size_t)s.M * 4));
+  a.piece_sum = (float*)((char*)a.piece_row + al256((size_t)a.blocks * 4));
+  a.piece_wgs = (a.blocks + 31) / 32 * 8;
   a.T = s.T;
   a.N = s.N;
   a.M = s.M;
@@ -634,15 +758,15 @@ hipError_t launch_expert_backward(const Shape& s, const void* x, const void* u, 
   if (e != hipSuccess) return e;
   int64_t sb = (s.rows + 3) / 4;
   if (sb > 16384) sb = 16384;
-  hipLaunchKernelGGL(bwd_score_kernel, dim3((unsigned)sb), dim3(256), 0, st, a);
+  a.score_wgs = (int)sb;
+  const int64_t adds = (int64_t)(a.blocks + kPieceGroup - 1) / kPieceGroup * 2 * ((s.d + 1023) / 1024);
+  hipLaunchKernelGGL(bwd_score_kernel, dim3((unsigned)(sb + adds)), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 
 namespace {
 
 constexpr int64_t kMaxBlocks = 1 << 22;  // past it the sum kernels walk the rest (a multiple of 8)
-
-size_t al256(size_t v) { return (v + 255) & ~(size_t)255; }
 
 // Tokens per tile of the picks: about 4096 tasks, or 1024 where that leaves fewer than 512
 // workgroups.

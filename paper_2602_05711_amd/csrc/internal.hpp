@@ -143,8 +143,8 @@ hipError_t launch_token_centric(const Shape& s, const void* x, const void* u, co
                                 hipStream_t st);
 
 // Backward of the expert compute: dx, per-active-expert du / dv rows (expert-major, from a
-// group-size-1 schedule), dgates and dscores. Workspace: backward_ws_bytes(M).
-size_t backward_ws_bytes(int64_t M);
+// group-size-1 schedule), dgates and dscores. Workspace: backward_ws_bytes(s).
+size_t backward_ws_bytes(const Shape& s);
 hipError_t launch_expert_backward(const Shape& s, const void* x, const void* u, const void* v,
                                   const int32_t* idx, const float* gates, const int32_t* perm,
                                   const int32_t* offsets, const int32_t* n_active,

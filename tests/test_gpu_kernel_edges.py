@@ -108,6 +108,86 @@ def test_expert_backward_segments(case):
     assert torch.isnan(out["du"][n:]).all() and torch.isnan(out["dv"][n:]).all()
 
 
+# (tasks of each expert in id order, d, dtype): segments of a piece of tasks (16 here, 32 from 32769 tasks on), one more, several,
+# that begin on a piece's edge and off it, one after the other and at the end; one and two experts per wave; every token
+# with one expert.
+PIECE_CASES = [((16, 17, 1, 33, 64, 2, 130), 200, "bf16"), ((300,), 2048, "bf16"), ((50, 16, 14, 20), 4096, "bf16"),
+               ((3, 3, 3, 3, 3, 47, 1, 1, 15, 16, 17, 18), 1032, "f32"), ((15,), 64, "bf16"), ((17, 15, 32, 16), 64, "f32"),
+               ((1,) * 36000 + (2000, 1, 1999), 16, "bf16")]
+
+
+@pytest.mark.parametrize("case", PIECE_CASES, ids=[f"{len(c[0])} experts, {c[1:]}" for c in PIECE_CASES])
+def test_expert_backward_pieces(case):
+    counts, d, dtype = case
+    T, nr = sum(counts), 192 if len(counts) > 1000 else 4
+    say(f"[expert backward, pieces] {len(counts)} experts, {T} tokens, d {d} {dtype}")
+    w = synth.Workload("piece", T=T, d=d, n_rows=nr, n_cols=nr, d_key=8, H=1, K=1, dtype=dtype)
+    inp = synth.make_inputs(w)
+    f = {k: synth.as_f32(v) for k, v in inp.items()}
+    rng = np.random.default_rng(T)
+    idx = rng.permutation(np.repeat(np.arange(len(counts)), counts)).reshape(T, 1, 1).astype(np.int32)
+    g = rng.random((T, 1, 1)).astype(np.float32)
+    dsc = oracle.desc(w)
+    perm, act, off, _ = oracle.schedule(dsc, idx)
+    dy = rng.standard_normal((T, d)).astype(np.float32)
+    ref = oracle.expert_backward(dsc, f["x"], f["u"], f["v"], idx, g.astype(np.float64), dy.astype(np.float64))
+    bnd = backward_error_bounds(f["x"], f["u"], f["v"], idx, g, dy, np.vectorize(lambda z: oracle.act(0, z)),
+                                np.vectorize(lambda z: oracle.act_grad(0, z)))
+    A, n = min(w.M, w.N), len(act)
+    offd = torch.full((A + 1,), -1, dtype=torch.int32, device="cuda")
+    offd[:n + 1] = to_dev(off)
+    dev, D = upload(inp), B.make_desc(w)
+    ws = P.workspace(D, B.STAGE_EXPERT_BACKWARD)
+    outs = []
+    for fill in (0, 255):  # the workspace's contents do not matter
+        ws.fill_(fill)
+        out = {k: torch.full(shape, float("nan"), device="cuda") for k, shape in
+               [("dx", (T, d)), ("du", (A, d)), ("dv", (A, d)), ("dgates", (T, 1, 1)), ("dscores", (T, 1, 1))]}
+        P.omnimoe_expert_backward(D, dev["x"], dev["u"], dev["v"], to_dev(idx), to_dev(g), to_dev(perm), offd,
+                                  torch.tensor([n], dtype=torch.int32, device="cuda"), to_dev(dy), out["dx"], out["du"],
+                                  out["dv"], out["dgates"], out["dscores"], ws=ws)
+        torch.cuda.synchronize()
+        assert torch.isnan(out["du"][n:]).all() and torch.isnan(out["dv"][n:]).all()
+        outs.append({k: v.cpu().numpy()[:n if k in ("du", "dv") else None] for k, v in out.items()})
+    for k, rk in (("dx", "dx"), ("du", "du_rows"), ("dv", "dv_rows"), ("dgates", "dgates"), ("dscores", "dscores")):
+        err = np.abs(outs[0][k].astype(np.float64) - ref[rk])
+        say(f"  {k}: max err / bound {(err / (2 * bnd[k] + 1e-30)).max():.2f}")
+        assert np.all(err <= 2 * bnd[k] + 1e-30), k
+        assert np.array_equal(outs[0][k].view(np.uint8), outs[1][k].view(np.uint8)), k
+
+
+def test_expert_backward_time_under_skew():
+    """One expert with a quarter of all tasks: its tasks are shared out, so the call takes a few times what it takes with
+    the tasks spread evenly (1.5 times here) and not the time of 16384 tasks one after another (30 times)."""
+    w = synth.Workload("hot", T=16384, d=512, n_rows=64, n_cols=64, d_key=8, H=1, K=4)
+    rng = np.random.default_rng(1)
+    even = torch.from_numpy((rng.permutation(w.M) % (w.N - 4) + 4).astype(np.int32).reshape(w.T, 1, 4))
+    hot = even.clone()
+    hot[:, 0, 0] = 1
+    dev = {k: torch.randn(s, device="cuda").to(torch.bfloat16) for k, s in
+           (("x", (w.T, w.d)), ("u", (w.N, w.d)), ("v", (w.N, w.d)))}
+    dy, D = torch.randn((w.T, w.d), device="cuda"), B.make_desc(w)
+    g = torch.full((w.T, 1, 4), 0.25, device="cuda")
+    ws = P.workspace(D, B.STAGE_EXPERT_BACKWARD)
+    out = [torch.empty(s, device="cuda") for s in ((w.T, w.d), (w.N, w.d), (w.N, w.d), (w.T, 1, 4), (w.T, 1, 4))]
+    ms = {}
+    for name, idx in (("even", even), ("hot", hot)):
+        idx = idx.cuda()
+        perm, act, off, na = (torch.empty(n, dtype=torch.int32, device="cuda") for n in (w.M, w.N, w.N + 1, 1))
+        P.omnimoe_schedule(D, idx, perm, act, off, na)
+        runs = []
+        for _ in range(8):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            P.omnimoe_expert_backward(D, dev["x"], dev["u"], dev["v"], idx, g, perm, off, na, dy, *out, ws=ws)
+            b.record()
+            torch.cuda.synchronize()
+            runs.append(a.elapsed_time(b))
+        ms[name] = sorted(runs)[3]
+    say(f"[expert backward] even {ms['even']:.3f} ms, one expert with a quarter of the tasks {ms['hot']:.3f} ms")
+    assert ms["hot"] <= 6 * ms["even"]
+
+
 # (T, d, d_key, n_rows, n_cols, H, K, query, dtype): blocks of 1, 2, 8 and 16 slots with partial ones, more than 64 picks per
 # token, a sub-key with hundreds of picks, tables of one row and of 4096; d_key pieces of 256 elements, whole and
 # partial, one to sixteen of them (combinations that eight divides and that it does not).
