@@ -508,7 +508,13 @@ __global__ __launch_bounds__(256) void select_kernel(SelectArgs a) {
 
 constexpr int kLargeMaxWaves = 8;  // workgroups of 256 or 512 threads
 constexpr int kMergeMinKeys = 1024;  // final order by merging the runs from k2 = 1024 keys on
-constexpr int kBucketMax = 64;       // fullest score bucket that is ranked key by key
+// Fullest score bucket that is ranked key by key: from about 50 keys on the merge or sort is the faster (rows of
+// 4096 + 4096 logits with one far outlier in each half, K = 4096: 4096 rows 6.1 ms with 64, 5.6 with 48; 24 costs 256 + 256
+// normal logits, K = 4096, 20%).
+constexpr int kBucketMax = 48;
+// Keys per bucket up to which a row is put in buckets at all (64 + 64 normal logits, K = 4096, all of the grid in 256
+// buckets: 916 us for 4096 rows that mostly failed, 763 without the attempt).
+constexpr int kBucketMean = 8;
 
 struct LargeArgs {
   const float* hs;
@@ -532,6 +538,7 @@ size_t large_lds_bytes(int n2, int k2, int kr) {
 
 struct LargeShared {
   int cnt[2][3][kLargeMaxWaves];  // per-wave partial counts, two buffers used in turn
+  int full;  // a score bucket has more than kBucketMax keys
   int wint[kLargeMaxWaves];
   float wsum[kLargeMaxWaves];
   uint64_t wmax[kLargeMaxWaves];
@@ -638,6 +645,13 @@ __device__ __forceinline__ void wave_sort256(uint64_t (&x)[4], int base) {
   ce_stage<7>(x, base, 256);
 }
 
+// The value, opaque to the compiler: what follows from it is not formed ahead of this point. (Formed ahead of
+// the row loop, the addresses and bounds of all of a row's phases were up to 145 spilled registers.)
+__device__ __forceinline__ int fresh(int v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+
 // RPT: row ranks per thread in the searches (kr <= RPT * NT). MERGE: the final order by merging
 // the runs (k2 >= 1024), else by a bitonic sort (k2 <= 512, four waves).
 template <int NT, int RPT, bool MERGE>
@@ -658,10 +672,10 @@ __global__ __launch_bounds__(NT, NT == 256 ? 5 : 4) void select_large_kernel(Lar
   // exclusive scan of t_a
   int* cnt_lo = (int*)((unsigned char*)sel_s + large_region_bytes_dev(n2, k2));  // [kr + 1]
   int* cnt_hi = cnt_lo + (kr + 1);                                                 // [kr + 1]
-  const int tid = threadIdx.x, l = lane_id(), w = tid >> 6;
   const uint64_t* ck = hk + n2;
 
   for (int64_t row = blockIdx.x; row < a.rows; row += gridDim.x) {
+    const int tid = fresh(threadIdx.x), l = tid & (kWave - 1), w = tid >> 6;
     const float* hr = a.hs + row * (int64_t)(a.nr + a.nc);
     // 1. the top kr row keys and top kc column keys, descending. Halves of at most 512 logits: two
     // waves per half, each 256 in its registers (so on all four SIMDs); longer halves: a
@@ -938,16 +952,19 @@ __global__ __launch_bounds__(NT, NT == 256 ? 5 : 4) void select_large_kernel(Lar
     // counts by LDS atomics, a scan, every key to any place of its bucket, and then each key's rank among
     // the few of its bucket gives its final place. The atomics' order only moves keys inside
     // a bucket, so the result does not depend on it. A row whose fullest bucket holds more than
-    // kBucketMax keys (ties, far outliers) is ordered by the runs below instead. It takes two passes of the
+    // kBucketMax keys (ties, far outliers) is ordered by the runs below instead; the waves look for that after one,
+    // two and four of a thread's keys, so that such a row stops counting early (all scores alike: every key's
+    // atomic goes to one counter). It takes two passes of the
     // keys through LDS and about a bucket's keys per key, against one pass per merge level or sort
-    // stage: selection of 4096 rows of the 320 x 320 grid, K = 4096 581 -> 492 us, K = 512 183 -> 163
-    // (with the half sorts on four waves 457 and 155).
+    // stage. Selection of 4096 rows of the 320 x 320 grid, by runs alone and now (us): normal logits, K = 4096
+    // 602 -> 422, K = 512 173 -> 138; scores alike, K = 4096 626 -> 614; rounded to quarters 1228 -> 1208.
     bool ordered = false;
-    {
+    const int nb = 4 * n2 < 2048 ? 4 * n2 : 2048;
+    if (K <= kBucketMean * nb) {
       constexpr int kPer = MERGE ? (NT == 512 ? 8 : 4) : 2;  // keys per thread: NT kPer >= k2 >= K
       int* cnt = (int*)smem;  // [nb]: the sorted halves are no longer needed
-      const int nb = 4 * n2 < 2048 ? 4 * n2 : 2048;
       for (int i = tid; i < nb; i += kLargeThreads) cnt[i] = 0;
+      if (tid == 0) sh.full = 0;
       // S_0 is row rank 0's first cell; the last selected cell of every row rank bounds S from below
       const double smax = f64_from_ord(sel_s[0]);
       double smin = smax;
@@ -983,28 +1000,24 @@ __global__ __launch_bounds__(NT, NT == 256 ? 5 : 4) void select_large_kernel(Lar
           es[q] = sel_s[i];
           en[q] = sel_n[i];
           const int b = bucket_of(es[q]);
-          ep[q] = (atomicAdd(&cnt[b], 1) << 16) | b;
+          const int at = atomicAdd(&cnt[b], 1);
+          if (at >= kBucketMax) sh.full = 1;
+          ep[q] = (at << 16) | b;
         }
+        // (waves that see it later go on a little: the counts of a row that ends up here are not used)
+        if ((q & (q + 1)) == 0 && q + 1 < kPer && *(volatile int*)&sh.full) break;
       }
       __syncthreads();
-      // exclusive scan of the counts (each thread a contiguous piece) and the fullest bucket
-      const int per = (nb + kLargeThreads - 1) / kLargeThreads, b0 = tid * per;
-      int loc = 0, full = 0;
-      for (int b = b0; b < b0 + per && b < nb; ++b) {
-        loc += cnt[b];
-        full = cnt[b] > full ? cnt[b] : full;
-      }
-      const int ex = wave_excl_scan_i32(loc);
-      const uint64_t over = __ballot(full > kBucketMax);
-      if (l == kWave - 1) sh.wint[w] = ex + loc;
-      if (l == 0) sh.cnt[0][0][w] = over != 0ull;
-      __syncthreads();
-      int run = ex, bad = 0;
-      for (int ww = 0; ww < kLargeWaves; ++ww) {
-        if (ww < w) run += sh.wint[ww];
-        bad |= sh.cnt[0][0][ww];
-      }
-      if (!bad) {
+      if (!sh.full) {
+        // exclusive scan of the counts (each thread a contiguous piece)
+        const int per = (nb + kLargeThreads - 1) / kLargeThreads, b0 = tid * per;
+        int loc = 0;
+        for (int b = b0; b < b0 + per && b < nb; ++b) loc += cnt[b];
+        const int ex = wave_excl_scan_i32(loc);
+        if (l == kWave - 1) sh.wint[w] = ex + loc;
+        __syncthreads();
+        int run = ex;
+        for (int ww = 0; ww < w; ++ww) run += sh.wint[ww];
         for (int b = b0; b < b0 + per && b < nb; ++b) {
           const int c = cnt[b];
           cnt[b] = run;

@@ -480,3 +480,52 @@ def test_select_large_orders(case):
     ri, _, rg, inexact = oracle.select_f32(oracle.desc(w), hs, oracle.BRUTE)
     assert inexact == 0 and np.array_equal(idx.cpu().numpy(), ri)
     np.testing.assert_allclose(g.cpu().numpy(), rg, rtol=GATE_TOL, atol=1e-7)
+
+
+# (n_rows, n_cols, K, kind, n): the order by score buckets at its edges: n equal scores around the fullest bucket that is ranked;
+# as many keys as the buckets take and one more; masked columns (a large negative value, or minus infinity) among the
+# picks, some of them and most; infinite and NaN logits at the top.
+BUCKET_CASES = [(1, 400, 300, "ties", 47), (1, 400, 300, "ties", 48), (1, 400, 300, "ties", 49), (1, 400, 400, "ties", 200),
+                (1, 3000, 2500, "ties", 49), (64, 64, 2048, "normal", 0), (64, 64, 2049, "normal", 0),
+                (64, 64, 4096, "normal", 0), (20, 300, 4096, "masked", 150), (20, 300, 4096, "masked", 290),
+                (20, 300, 4096, "-inf", 150), (20, 300, 300, "-inf", 290), (20, 300, 500, "+inf", 1),
+                (320, 320, 4096, "+inf", 3), (40, 300, 700, "nan", 2)]
+
+
+@pytest.mark.parametrize("case", BUCKET_CASES, ids=[str(c) for c in BUCKET_CASES])
+def test_select_large_buckets(case):
+    nr, nc, K, kind, n = case
+    say(f"[select, buckets] {case}")
+    rng = np.random.default_rng(nr + nc + K + n)
+    T = 5
+    hs = rng.standard_normal((T, 1, nr + nc)).astype(np.float32)
+    if kind == "ties":  # evenly spread scores, n of them alike (in shuffled places, among the best K)
+        hs[..., :nr] = 0.0
+        for t in range(T):
+            c = np.linspace(4.0, -4.0, nc).astype(np.float32)
+            c[50:50 + n] = c[50]
+            hs[t, 0, nr:] = rng.permutation(c)
+    if kind == "masked":
+        hs = np.round(hs * 1024) / 1024  # (sums with the mask stay exact in double)
+    put = {"masked": -2.0 ** 30, "-inf": -np.inf, "+inf": np.inf, "nan": np.nan}.get(kind)
+    if put is not None:
+        for t in range(T):
+            hs[t, 0, nr + rng.permutation(nc)[:n]] = put
+    w = synth.Workload("sel", T=T, d=16, n_rows=nr, n_cols=nc, d_key=8, H=1, K=K, dtype="f32")
+    idx = torch.empty((T, 1, K), dtype=torch.int32, device="cuda")
+    g = torch.empty((T, 1, K), dtype=torch.float32, device="cuda")
+    P.omnimoe_select(B.make_desc(w), to_dev(hs), idx, g)
+    torch.cuda.synchronize()
+    got, gg = idx.cpu().numpy()[:, 0], g.cpu().numpy()[:, 0]
+    # scores as sums of two fp32 in double (exact here), NaN above plus infinity; ties to the lower id
+    s = (hs[:, 0, :nr, None].astype(np.float64) + hs[:, 0, None, nr:].astype(np.float64)).reshape(T, -1)
+    for t in range(T):
+        key = np.where(np.isnan(s[t]), np.inf, s[t])
+        order = np.lexsort((np.arange(nr * nc), -key, ~np.isnan(s[t])))[:K]
+        # (scores of minus infinity: any of them, since the order among rows and columns is not that among their sums)
+        m = int(np.isfinite(s[t][order]).sum()) if kind == "-inf" else K
+        assert np.array_equal(got[t][:m], order[:m]), t
+        assert len(set(got[t])) == K and np.all(s[t][got[t][m:]] == -np.inf)
+        if kind not in ("+inf", "nan"):
+            e = np.exp(s[t][order] - s[t][order[0]])
+            np.testing.assert_allclose(gg[t], e / e.sum(), rtol=GATE_TOL, atol=1e-7)
