@@ -311,7 +311,7 @@ omnimoe_status omnimoe_route_backward(const omnimoe_layer_desc* desc, const void
  * cache, or of at most 256 MiB with at most six tasks per expert), no schedule is formed: the same
  * a_p are computed in slot order, with identical results (by the selection kernel itself when there
  * are at least 256 (token, head) rows, or, with enough tokens, in one kernel with the routed sum,
- * whose time OMNIMOE_KERNEL_ACCUMULATE then holds; omnimoe_layer_path tells which kernels run).
+ * whose time OMNIMOE_KERNEL_ACCUMULATE then holds; omnimoe_layer_kernels tells which kernels run).
  * With at least 512 tokens, two tasks per expert and tables of at most 256 MiB whose rows are 2, 4
  * or 8 KiB, every token's tasks are put in one order of the experts instead and swept by all tokens
  * together (OMNIMOE_KERNEL_SCHEDULE times that ordering): the sums run in another fixed order, so y
@@ -333,20 +333,31 @@ omnimoe_status omnimoe_layer_forward(const omnimoe_layer_desc* desc, const void*
  * NULL path. The result depends only on the descriptor, so it can be taken once per shape. */
 typedef enum {
   OMNIMOE_PATH_SCHEDULE = 1,   /* the tasks are put in expert order: the expert-major schedule
-                                  (Eq. 12-13), or each token's tasks for the sweeps; without it
-                                  the a_p are formed in slot order */
+                                  (Eq. 12-13), or (omnimoe_layer_path only) each token's tasks for
+                                  the sweeps; without it the a_p are formed in slot order */
   OMNIMOE_PATH_GROUPED = 2,    /* a_p from the grouped GEMM of Eq. 14 (group_size > 1) */
   OMNIMOE_PATH_SELECT_DOT = 4, /* the selection kernel also forms the slot-order a_p (no separate
                                   dot launch; the OMNIMOE_KERNEL_SELECT time includes it) */
   OMNIMOE_PATH_DENSE_SUM = 8,  /* the routed sum as one dense product over all experts (one head,
                                   K >= N / 64) */
-  OMNIMOE_PATH_DENSE_DOT = 16  /* with groups of one expert, the a_p as well: x . u for every
+  OMNIMOE_PATH_DENSE_DOT = 16, /* with groups of one expert, the a_p as well: x . u for every
                                   (token, expert) pair on the MFMA kernel, gate and activation
                                   kept at the selected pairs only (Eq. 14 with a single group;
                                   no schedule; OMNIMOE_KERNEL_SCHEDULE times the selection-mask
                                   pass, OMNIMOE_KERNEL_EXPERT_DOT this product) */
+  /* omnimoe_layer_kernels only: */
+  OMNIMOE_PATH_TOKEN_STAGE = 1 << 16, /* slot-order a_p and routed sum in one kernel
+                                         (OMNIMOE_KERNEL_EXPERT_DOT launches nothing) */
+  OMNIMOE_PATH_SWEEP_STAGE = 1 << 17, /* a_p and routed sum in sweeps; no schedule
+                                         (OMNIMOE_KERNEL_SCHEDULE times the tokens' order) */
+  OMNIMOE_PATH_SWEEP_SUM = 1 << 18    /* with groups: the routed sum in sweeps (its order counts
+                                         under OMNIMOE_KERNEL_ACCUMULATE) */
 } omnimoe_path_flag;
 omnimoe_status omnimoe_layer_path(const omnimoe_layer_desc* desc, int32_t* path);
+
+/* omnimoe_layer_path with the form of the expert stage: the flags above from 1 << 16 on as well,
+ * and OMNIMOE_PATH_SCHEDULE only where an expert-major schedule is formed; -1 for a bad descriptor. */
+int32_t omnimoe_layer_kernels(const omnimoe_layer_desc* desc);
 
 /* For callers that cannot allocate device memory (code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc): omnimoe_layer_forward with its workspace taken from

@@ -83,6 +83,7 @@ def load_library():
         "omnimoe_layer_forward": [D, P, P, P, P, P, P, P, P, P, SZ, P],
         "omnimoe_layer_forward_noalloc": [D, P, P, P, P, P, P, P, P, P],
         "omnimoe_layer_path": [D, ctypes.POINTER(I32)],
+        "omnimoe_layer_kernels": [D],
         "omnimoe_layer_forward_timed": [D, P, P, P, P, P, P, P, P, P, SZ, P, P],
         "omnimoe_timer_create": [I32, ctypes.POINTER(P)],
         "omnimoe_timer_destroy": [P],
@@ -267,6 +268,7 @@ NOALLOC_SCRATCH_BYTES = 64 * 1024 * 1024  # OMNIMOE_NOALLOC_SCRATCH_BYTES
 
 # omnimoe_path_flag
 PATH_SCHEDULE, PATH_GROUPED, PATH_SELECT_DOT, PATH_DENSE_SUM, PATH_DENSE_DOT = 1, 2, 4, 8, 16
+PATH_TOKEN_STAGE, PATH_SWEEP_STAGE, PATH_SWEEP_SUM = 1 << 16, 1 << 17, 1 << 18  # omnimoe_layer_kernels only
 
 
 def omnimoe_layer_path(desc):
@@ -275,6 +277,14 @@ def omnimoe_layer_path(desc):
     _check("omnimoe_layer_path", load_library().omnimoe_layer_path(ctypes.byref(desc),
                                                                     ctypes.byref(out)))
     return out.value
+
+
+def omnimoe_layer_kernels(desc):
+    """omnimoe_layer_path with the form of the expert stage (the flags from PATH_TOKEN_STAGE on)."""
+    flags = load_library().omnimoe_layer_kernels(ctypes.byref(desc))
+    if flags < 0:
+        raise OmnimoeError("omnimoe_layer_kernels", 1, "invalid argument")
+    return flags
 
 
 def omnimoe_layer_forward_noalloc(desc, x, keys_row, keys_col, u, v, y, idx_out=None,

@@ -93,7 +93,7 @@ size_t active_bytes(const Shape& s) { return align_up((size_t)(std::min(s.M, s.N
 bool grouped_supported(const Shape& s) { return s.bf16 && s.d % 64 == 0; }
 bool layer_grouped(const Shape& s) { return s.B > 1 && grouped_supported(s); }
 
-// Which kernels the layer runs for a shape (omnimoe_layer_path reports the same flags).
+// Which kernels the layer runs for a shape (omnimoe_layer_kernels reports these flags).
 // Where the expert-major order saves no memory traffic (a decode step; at most one task per two
 // experts; or a u table that fits in the MALL) the layer takes the slot-order dot and forms no
 // schedule. With at least kSelectDotMinRows (token, head) rows the selection kernel forms that
@@ -103,14 +103,8 @@ constexpr int64_t kSelectDotMinRows = 256;
 // Up to this many tasks the sort by expert is one launch, as cheap as the flag pass and scan
 // that replace it above (launch_group_schedule).
 constexpr int64_t kSortFreeMinTasks = 8192;
-// The slot-order dot and the routed sum in one kernel (not among the reported flags: like them it
-// forms no schedule).
-constexpr int32_t kPathTokenStage = 1 << 16;
-// Dots and sum, or with groups the sum, in sweeps over the experts (the tasks of every token are put
-// in an order of the experts first: reported as a schedule).
-constexpr int32_t kPathSweepStage = 1 << 17;
-constexpr int32_t kPathSweepSum = 1 << 18;
-constexpr int32_t kPathReported = (1 << 16) - 1;
+// omnimoe_layer_path reports the flags below this bit (and a sweep as a schedule), omnimoe_layer_kernels all.
+constexpr int32_t kPathReported = OMNIMOE_PATH_TOKEN_STAGE - 1;
 
 // The sweeps pay from two tasks per expert and 512 tokens on. Expert stage on 320^2 experts of
 // d = 1024 (us, the former kernels and the sweeps): K = 128 (1.3 tasks per expert at 1024
@@ -150,11 +144,11 @@ int32_t layer_path(const Shape& s) {
   if (omnimoe::dense_accumulate(s)) f |= OMNIMOE_PATH_DENSE_SUM;
   if (unscheduled && !(f & (OMNIMOE_PATH_SELECT_DOT | OMNIMOE_PATH_DENSE_SUM)) &&
       omnimoe::token_stage(s))
-    f |= kPathTokenStage;
+    f |= OMNIMOE_PATH_TOKEN_STAGE;
   if (!(f & (OMNIMOE_PATH_SELECT_DOT | OMNIMOE_PATH_DENSE_SUM)) && sweep_pays(s)) {
-    if (grouped && sweep_fits(s, sweep_sum_late_bytes(s))) f |= kPathSweepSum;
+    if (grouped && sweep_fits(s, sweep_sum_late_bytes(s))) f |= OMNIMOE_PATH_SWEEP_SUM;
     if (!grouped && sweep_fits(s, omnimoe::sweep_stage_ws_bytes(s)))
-      f = OMNIMOE_PATH_SCHEDULE | kPathSweepStage;
+      f = OMNIMOE_PATH_SWEEP_STAGE;
   }
   // Both products dense over all experts: no schedule and no per-task dot.
   if (omnimoe::dense_dot(s)) f = OMNIMOE_PATH_DENSE_SUM | OMNIMOE_PATH_DENSE_DOT;
@@ -214,8 +208,8 @@ size_t stage_bytes(const Shape& s, int stage) {
       // Both products dense: only their buffers, after the logits are dead.
       if (layer_path(s) & OMNIMOE_PATH_DENSE_DOT) late = omnimoe::dense_dot_ws_bytes(s);
       // The sweeps: their list (and partial dots) after the logits are dead; with groups, after a[].
-      if (layer_path(s) & kPathSweepStage) late = omnimoe::sweep_stage_ws_bytes(s);
-      if (layer_path(s) & kPathSweepSum) late = sweep_sum_late_bytes(s);
+      if (layer_path(s) & OMNIMOE_PATH_SWEEP_STAGE) late = omnimoe::sweep_stage_ws_bytes(s);
+      if (layer_path(s) & OMNIMOE_PATH_SWEEP_SUM) late = sweep_sum_late_bytes(s);
       return fixed_bytes(s) + std::max(hs_bytes(s), late);
     }
   }
@@ -290,7 +284,7 @@ omnimoe_status layer_impl(const omnimoe_layer_desc* desc, const void* x, const v
     if (timer) ++timer->used;
     return OMNIMOE_OK;
   }
-  if (path & kPathSweepStage) {
+  if (path & OMNIMOE_PATH_SWEEP_STAGE) {
     if ((e = omnimoe::launch_sweep_order(s, idx, late, strm))) return hip_status(e);
     mark(3);
     if ((e = omnimoe::launch_sweep_dot(s, x, u, gates, late, strm))) return hip_status(e);
@@ -314,7 +308,7 @@ omnimoe_status layer_impl(const omnimoe_layer_desc* desc, const void* x, const v
     if (e) return hip_status(e);
   }
   mark(3);
-  if (path & kPathTokenStage) {
+  if (path & OMNIMOE_PATH_TOKEN_STAGE) {
     mark(4);
     if ((e = omnimoe::launch_token_stage(s, x, u, v, idx, gates, y, strm))) return hip_status(e);
     mark(5);
@@ -338,7 +332,7 @@ omnimoe_status layer_impl(const omnimoe_layer_desc* desc, const void* x, const v
   }
   mark(4);
   void* const sum_ws = (char*)abuf + m_bytes(s);
-  e = path & kPathSweepSum ? omnimoe::launch_sweep_sum(s, v, idx, abuf, y, sum_ws, strm)
+  e = path & OMNIMOE_PATH_SWEEP_SUM ? omnimoe::launch_sweep_sum(s, v, idx, abuf, y, sum_ws, strm)
                            : routed_sum(s, v, idx, abuf, y, sum_ws, strm);
   if (e) return hip_status(e);
   mark(5);
@@ -707,8 +701,14 @@ omnimoe_status omnimoe_layer_path(const omnimoe_layer_desc* desc, int32_t* path)
   omnimoe_status st = check_desc(desc, &s);
   if (st) return st;
   if (!path) return OMNIMOE_ERR_INVALID_ARG;
-  *path = layer_path(s) & kPathReported;
+  const int32_t f = layer_path(s);
+  *path = (f & kPathReported) | (f & OMNIMOE_PATH_SWEEP_STAGE ? OMNIMOE_PATH_SCHEDULE : 0);
   return OMNIMOE_OK;
+}
+
+int32_t omnimoe_layer_kernels(const omnimoe_layer_desc* desc) {
+  Shape s;
+  return check_desc(desc, &s) ? -1 : layer_path(s);
 }
 
 omnimoe_status omnimoe_layer_forward_noalloc(const omnimoe_layer_desc* desc, const void* x,

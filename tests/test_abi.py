@@ -252,3 +252,25 @@ def test_layer_path_flags():
     with pytest.raises(P.OmnimoeError):
         P.omnimoe_layer_path(bad)
     assert P.load_library().omnimoe_layer_path(ctypes.byref(bad), None) == INVALID
+
+
+def test_layer_kernels_flags():
+    # omnimoe_layer_path's flags with the form of the expert stage: no other bits, and a schedule only where one is formed
+    def flags(name, **kw):
+        D = B.make_desc(synth.WORKLOADS[name].with_(**kw))
+        k, p = B.omnimoe_layer_kernels(D), P.omnimoe_layer_path(D)
+        assert k & 0xFFFF == (p & ~B.PATH_SCHEDULE if k & B.PATH_SWEEP_STAGE else p)
+        return k
+
+    assert flags("train_bf16") == B.PATH_SCHEDULE and flags("decode1_bf16") == 0
+    assert flags("decode64_bf16") == B.PATH_SELECT_DOT and flags("small_bf16") == B.PATH_SELECT_DOT
+    assert flags("tiny_f32") == B.PATH_TOKEN_STAGE and flags("tiny_f32", T=47) == 0
+    assert flags("paper_k512_bf16") == B.PATH_SWEEP_STAGE
+    assert flags("paper_k512_bf16", T=511) == B.PATH_TOKEN_STAGE
+    assert flags("paper_k512_bf16", group_size=64) == B.PATH_SCHEDULE | B.PATH_GROUPED | B.PATH_SWEEP_SUM
+    assert flags("paper_k4096_bf16") == B.PATH_DENSE_SUM | B.PATH_DENSE_DOT
+    bad = B.make_desc(synth.WORKLOADS["small_bf16"])
+    bad.K = 0
+    with pytest.raises(P.OmnimoeError):
+        B.omnimoe_layer_kernels(bad)
+    assert P.load_library().omnimoe_layer_kernels(None) == -1

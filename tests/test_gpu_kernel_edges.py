@@ -278,7 +278,7 @@ def test_token_stage_layer(case):
     w = synth.Workload("stage", T=T, d=d, n_rows=nr, n_cols=nc, d_key=16, H=H, K=K, dtype=dtype, act=act)
     inp = synth.make_inputs(w)
     dev, D = upload(inp), B.make_desc(w)
-    assert not one or not B.omnimoe_layer_path(D) & B.PATH_SCHEDULE
+    assert bool(B.omnimoe_layer_kernels(D) & B.PATH_TOKEN_STAGE) == one
     y = torch.full((T, d), float("nan"), device="cuda")
     idx = torch.empty((T, H, K), dtype=torch.int32, device="cuda")
     g = torch.empty((T, H, K), device="cuda")
@@ -297,26 +297,28 @@ def test_token_stage_layer(case):
         assert np.array_equal(got.view(np.uint8), y_tc.cpu().numpy().view(np.uint8))
 
 
-# (T, d, n_rows, n_cols, H, K, dtype, act, group size): the expert stage in sweeps in the layer (at least 512 tokens, two tasks per
-# expert, rows of 2, 4 and 8 KiB): tokens that a workgroup's share does not divide, one walk and more than one per lane
-# group, four waves and sixteen in step, slots that sixteen and 64 do not divide, fewer than sixteen; with groups (the sum
-# alone), and just below the line.
-SWEEP_CASES = [(512, 1024, 8, 9, 2, 7, "bf16", "gelu", 1), (515, 2048, 30, 31, 2, 21, "bf16", "silu", 1),
-               (2051, 1024, 40, 41, 3, 23, "bf16", "gelu", 1), (1030, 2048, 7, 9, 1, 16, "f32", "gelu", 1),
-               (517, 4096, 6, 7, 2, 17, "bf16", "gelu", 1), (4200, 512, 9, 9, 1, 1, "f32", "gelu", 1),
-               (9000, 1024, 5, 6, 2, 3, "bf16", "gelu", 1), (700, 1024, 20, 21, 2, 80, "bf16", "gelu", 16),
-               (2100, 1024, 50, 60, 2, 33, "bf16", "silu", 64), (511, 1024, 8, 9, 2, 7, "bf16", "gelu", 1),
-               (512, 1024, 50, 60, 1, 11, "bf16", "gelu", 1)]
+# (T, d, n_rows, n_cols, H, K, dtype, act, group size, swept): the expert stage in sweeps in the layer (at least 512 tokens, two
+# tasks per expert, rows of 2, 4 and 8 KiB): tokens that a workgroup's share does not divide, one walk and more than one
+# per lane group, four waves and sixteen in step, slots that sixteen and 64 do not divide, fewer than sixteen; with groups
+# (the sum alone), and just below the line.
+SWEEP_CASES = [(512, 1024, 8, 9, 2, 7, "bf16", "gelu", 1, "stage"), (515, 2048, 30, 31, 2, 21, "bf16", "silu", 1, "stage"),
+               (2051, 1024, 40, 41, 3, 23, "bf16", "gelu", 1, "stage"), (1030, 2048, 7, 9, 1, 16, "f32", "gelu", 1, "stage"),
+               (517, 4096, 6, 7, 2, 17, "bf16", "gelu", 1, "stage"), (4200, 512, 9, 9, 1, 1, "f32", "gelu", 1, "stage"),
+               (9000, 1024, 5, 6, 2, 3, "bf16", "gelu", 1, "stage"), (700, 1024, 20, 21, 2, 80, "bf16", "gelu", 16, "sum"),
+               (2100, 1024, 50, 60, 2, 33, "bf16", "silu", 64, "sum"), (511, 1024, 8, 9, 2, 7, "bf16", "gelu", 1, ""),
+               (512, 1024, 50, 60, 1, 11, "bf16", "gelu", 1, "")]
 
 
 @pytest.mark.parametrize("case", SWEEP_CASES, ids=[str(c) for c in SWEEP_CASES])
 def test_sweep_layer(case):
-    T, d, nr, nc, H, K, dtype, act, Bg = case
+    T, d, nr, nc, H, K, dtype, act, Bg, swept = case
     say(f"[sweep] {case}")
     w = synth.Workload("sweep", T=T, d=d, n_rows=nr, n_cols=nc, d_key=16, H=H, K=K, dtype=dtype, act=act,
                        group_size=Bg)
     inp = synth.make_inputs(w)
     dev, D = upload(inp), B.make_desc(w)
+    assert B.omnimoe_layer_kernels(D) & (B.PATH_SWEEP_STAGE | B.PATH_SWEEP_SUM) == {
+        "stage": B.PATH_SWEEP_STAGE, "sum": B.PATH_SWEEP_SUM, "": 0}[swept]
     ws = P.workspace(D, B.STAGE_LAYER)
     ys = []
     for fill in (0, 255):  # the workspace's contents do not matter
@@ -348,6 +350,7 @@ def test_sweep_tail_adds_nothing(case):
     say(f"[sweep tail] {case}")
     w = synth.Workload("tail", T=T, d=1024, n_rows=7, n_cols=9, d_key=16, H=H, K=K)
     dev, D = upload(synth.make_inputs(w)), B.make_desc(w)
+    assert B.omnimoe_layer_kernels(D) & B.PATH_SWEEP_STAGE
     # an overflowed value of every expert in a column of its own: the sum there is infinite where the token picked that
     # expert and finite elsewhere (zero times such a row would be NaN)
     e = torch.arange(w.N, device="cuda")
