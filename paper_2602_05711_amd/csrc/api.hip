@@ -118,19 +118,23 @@ bool sweep_pays(const Shape& s) {
 
 size_t sched_or_plan_bytes(const Shape& s);
 
-// Layer workspace behind the fixed buffers without and with the sweeps. A shape that the sweeps
-// would take past the static scratch of omnimoe_layer_forward_noalloc keeps the former kernels.
 size_t late_bytes(const Shape& s) {
   return sched_or_plan_bytes(s) + m_bytes(s) + omnimoe::dense_accumulate_ws_bytes(s);
 }
 size_t fixed_bytes(const Shape& s) { return 3 * m_bytes(s) + 2 * active_bytes(s) + 256; }
-bool sweep_fits(const Shape& s, size_t late) {
-  const size_t limit = (size_t)OMNIMOE_NOALLOC_SCRATCH_BYTES;
-  return fixed_bytes(s) + std::max(hs_bytes(s), late) <= limit ||
-         fixed_bytes(s) + std::max(hs_bytes(s), late_bytes(s)) > limit;
-}
-size_t sweep_sum_late_bytes(const Shape& s) {
-  return sched_or_plan_bytes(s) + m_bytes(s) + omnimoe::sweep_sum_ws_bytes(s);
+
+// Tokens per pass of the swept dots. Their partial sums take 32 bytes a task, more than the other kernels' buffers
+// (at least 24), so a layer that would pass the static scratch of omnimoe_layer_forward_noalloc by them alone
+// takes its dots in two passes; each token's results are the same. 320^2 experts of d = 1024, K = 512, layer
+// (us, schedule and two passes): 2496 tokens 741 and 603, 3000 tokens 877 and 647, 3500 tokens 1025 and 690.
+int64_t sweep_tokens(const Shape& s) {
+  const size_t limit = (size_t)OMNIMOE_NOALLOC_SCRATCH_BYTES, fixed = fixed_bytes(s);
+  if (fixed + std::max(hs_bytes(s), omnimoe::sweep_stage_ws_bytes(s, s.T)) <= limit ||
+      fixed + std::max(hs_bytes(s), late_bytes(s)) > limit)
+    return s.T;
+  int64_t n = 2;
+  while (n < s.T && fixed + omnimoe::sweep_stage_ws_bytes(s, (s.T + n - 1) / n) > limit) ++n;
+  return (s.T + n - 1) / n;
 }
 
 int32_t layer_path(const Shape& s) {
@@ -146,9 +150,8 @@ int32_t layer_path(const Shape& s) {
       omnimoe::token_stage(s))
     f |= OMNIMOE_PATH_TOKEN_STAGE;
   if (!(f & (OMNIMOE_PATH_SELECT_DOT | OMNIMOE_PATH_DENSE_SUM)) && sweep_pays(s)) {
-    if (grouped && sweep_fits(s, sweep_sum_late_bytes(s))) f |= OMNIMOE_PATH_SWEEP_SUM;
-    if (!grouped && sweep_fits(s, omnimoe::sweep_stage_ws_bytes(s)))
-      f = OMNIMOE_PATH_SWEEP_STAGE;
+    if (grouped) f |= OMNIMOE_PATH_SWEEP_SUM;
+    else f = OMNIMOE_PATH_SWEEP_STAGE;
   }
   // Both products dense over all experts: no schedule and no per-task dot.
   if (omnimoe::dense_dot(s)) f = OMNIMOE_PATH_DENSE_SUM | OMNIMOE_PATH_DENSE_DOT;
@@ -207,9 +210,10 @@ size_t stage_bytes(const Shape& s, int stage) {
         late = hs_bytes(s) + m_bytes(s) + omnimoe::dense_accumulate_ws_bytes(s);
       // Both products dense: only their buffers, after the logits are dead.
       if (layer_path(s) & OMNIMOE_PATH_DENSE_DOT) late = omnimoe::dense_dot_ws_bytes(s);
-      // The sweeps: their list (and partial dots) after the logits are dead; with groups, after a[].
-      if (layer_path(s) & OMNIMOE_PATH_SWEEP_STAGE) late = omnimoe::sweep_stage_ws_bytes(s);
-      if (layer_path(s) & OMNIMOE_PATH_SWEEP_SUM) late = sweep_sum_late_bytes(s);
+      // The sweeps: their list and partial dots after the logits are dead. (With groups the swept sum's list
+      // takes the place of the sort buffers.)
+      if (layer_path(s) & OMNIMOE_PATH_SWEEP_STAGE)
+        late = omnimoe::sweep_stage_ws_bytes(s, sweep_tokens(s));
       return fixed_bytes(s) + std::max(hs_bytes(s), late);
     }
   }
@@ -287,7 +291,7 @@ omnimoe_status layer_impl(const omnimoe_layer_desc* desc, const void* x, const v
   if (path & OMNIMOE_PATH_SWEEP_STAGE) {
     if ((e = omnimoe::launch_sweep_order(s, idx, late, strm))) return hip_status(e);
     mark(3);
-    if ((e = omnimoe::launch_sweep_dot(s, x, u, gates, late, strm))) return hip_status(e);
+    if ((e = omnimoe::launch_sweep_dot(s, sweep_tokens(s), x, u, gates, late, strm))) return hip_status(e);
     mark(4);
     if ((e = omnimoe::launch_sweep_sorted_sum(s, v, y, late, strm))) return hip_status(e);
     mark(5);
@@ -331,9 +335,10 @@ omnimoe_status layer_impl(const omnimoe_layer_desc* desc, const void* x, const v
     return hip_status(e);
   }
   mark(4);
-  void* const sum_ws = (char*)abuf + m_bytes(s);
-  e = path & OMNIMOE_PATH_SWEEP_SUM ? omnimoe::launch_sweep_sum(s, v, idx, abuf, y, sum_ws, strm)
-                           : routed_sum(s, v, idx, abuf, y, sum_ws, strm);
+  // (the swept sum's list, 8 bytes a task, takes the place of the sort buffers, at least 20)
+  e = path & OMNIMOE_PATH_SWEEP_SUM
+          ? omnimoe::launch_sweep_sum(s, v, idx, abuf, y, late, strm)
+          : routed_sum(s, v, idx, abuf, y, (char*)abuf + m_bytes(s), strm);
   if (e) return hip_status(e);
   mark(5);
   if (timer) ++timer->used;

@@ -223,16 +223,15 @@ hipError_t launch_token_stage(const Shape& s, const void* x, const void* u, cons
                               const int32_t* idx, const float* gates, float* y, hipStream_t st);
 
 // The expert stage in sweeps over the experts, an eighth of the columns to an XCD (sweep.hip):
-// the routed sum from a given a[] (order and sum), or order, dots (with the activation) and sum of
-// the list that they leave in ws.
+// the routed sum from a given a[] (order and sum; 8 M bytes of ws), or order, dots (with the activation, `tokens`
+// tokens at a time) and sum of the list that they leave in ws.
 bool sweepable(const Shape& s);
-size_t sweep_sum_ws_bytes(const Shape& s);
 hipError_t launch_sweep_sum(const Shape& s, const void* v, const int32_t* idx, const float* abuf,
                             float* y, void* ws, hipStream_t st);
-size_t sweep_stage_ws_bytes(const Shape& s);
+size_t sweep_stage_ws_bytes(const Shape& s, int64_t tokens);
 hipError_t launch_sweep_order(const Shape& s, const int32_t* idx, void* ws, hipStream_t st);
-hipError_t launch_sweep_dot(const Shape& s, const void* x, const void* u, const float* gates,
-                            void* ws, hipStream_t st);
+hipError_t launch_sweep_dot(const Shape& s, int64_t tokens, const void* x, const void* u,
+                            const float* gates, void* ws, hipStream_t st);
 hipError_t launch_sweep_sorted_sum(const Shape& s, const void* v, float* y, void* ws,
                                    hipStream_t st);
 

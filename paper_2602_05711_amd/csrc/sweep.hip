@@ -309,9 +309,8 @@ bool sweepable(const Shape& s) {
          s.N * chunks * 16 <= kSweepMaxTableBytes;
 }
 
-size_t sweep_sum_ws_bytes(const Shape& s) { return al256((size_t)s.M * 8); }
-size_t sweep_stage_ws_bytes(const Shape& s) {
-  return al256((size_t)s.M * 8) + al256((size_t)s.M * 4 * kSlices);
+size_t sweep_stage_ws_bytes(const Shape& s, int64_t tokens) {
+  return al256((size_t)s.M * 8) + al256((size_t)tokens * s.hk * 4 * kSlices);
 }
 
 hipError_t launch_sweep_sum(const Shape& s, const void* v, const int32_t* idx, const float* abuf,
@@ -335,19 +334,23 @@ hipError_t launch_sweep_order(const Shape& s, const int32_t* idx, void* ws, hipS
   return hipGetLastError();
 }
 
-hipError_t launch_sweep_dot(const Shape& s, const void* x, const void* u, const float* gates,
-                            void* ws, hipStream_t st) {
+hipError_t launch_sweep_dot(const Shape& s, int64_t tokens, const void* x, const void* u,
+                            const float* gates, void* ws, hipStream_t st) {
   SweepArgs a = sweep_args(s);
-  a.x = (const uint4*)x;
-  a.gates = gates;
-  a.list = (int2*)ws;
   a.part = (float*)((char*)ws + al256((size_t)s.M * 8));
   a.table = (const uint4*)u;
-  hipError_t e = run_sweep(a, s.bf16, true, st);
-  if (e != hipSuccess) return e;
-  const int64_t blocks = (s.M + 255) / 256;
-  hipLaunchKernelGGL(sweep_act_kernel, dim3((unsigned)(blocks < 65536 ? blocks : 65536)), dim3(256), 0,
-                     st, a);
+  for (int64_t t0 = 0; t0 < s.T; t0 += tokens) {
+    a.T = s.T - t0 < tokens ? s.T - t0 : tokens;
+    a.M = a.T * s.hk;
+    a.x = (const uint4*)x + t0 * a.chunks;
+    a.gates = gates + t0 * s.hk;
+    a.list = (int2*)ws + t0 * s.hk;
+    hipError_t e = run_sweep(a, s.bf16, true, st);
+    if (e != hipSuccess) return e;
+    const int64_t blocks = (a.M + 255) / 256;
+    hipLaunchKernelGGL(sweep_act_kernel, dim3((unsigned)(blocks < 65536 ? blocks : 65536)), dim3(256), 0,
+                       st, a);
+  }
   return hipGetLastError();
 }
 

@@ -274,3 +274,18 @@ def test_layer_kernels_flags():
     with pytest.raises(P.OmnimoeError):
         B.omnimoe_layer_kernels(bad)
     assert P.load_library().omnimoe_layer_kernels(None) == -1
+
+
+def test_sweeps_hold_at_every_length():
+    # From 512 tokens and two tasks per expert on the layer is swept; and the layers that the library's static scratch
+    # holds are those up to one length.
+    w = synth.WORKLOADS["paper_k512_bf16"]
+    for K, group in ((512, 1), (128, 1), (512, 64), (128, 64)):
+        held = True
+        for T in range(2048, 15000, 61):
+            D = B.make_desc(w.with_(T=T, K=K, group_size=group))
+            assert B.omnimoe_layer_kernels(D) & (B.PATH_SWEEP_STAGE | B.PATH_SWEEP_SUM), (K, group, T)
+            fits = _ws(D)[1] <= B.NOALLOC_SCRATCH_BYTES
+            assert held or not fits, (K, group, T)
+            held = fits
+        assert not held

@@ -299,12 +299,13 @@ def test_token_stage_layer(case):
 
 # (T, d, n_rows, n_cols, H, K, dtype, act, group size, swept): the expert stage in sweeps in the layer (at least 512 tokens, two
 # tasks per expert, rows of 2, 4 and 8 KiB): tokens that a workgroup's share does not divide, one walk and more than one
-# per lane group, four waves and sixteen in step, slots that sixteen and 64 do not divide, fewer than sixteen; with groups
-# (the sum alone), and just below the line.
+# per lane group, four waves and sixteen in step, slots that sixteen and 64 do not divide, fewer than sixteen; the dots in
+# two passes (layers that one pass would take past 64 MiB); with groups (the sum alone), and just below the line.
 SWEEP_CASES = [(512, 1024, 8, 9, 2, 7, "bf16", "gelu", 1, "stage"), (515, 2048, 30, 31, 2, 21, "bf16", "silu", 1, "stage"),
                (2051, 1024, 40, 41, 3, 23, "bf16", "gelu", 1, "stage"), (1030, 2048, 7, 9, 1, 16, "f32", "gelu", 1, "stage"),
                (517, 4096, 6, 7, 2, 17, "bf16", "gelu", 1, "stage"), (4200, 512, 9, 9, 1, 1, "f32", "gelu", 1, "stage"),
-               (9000, 1024, 5, 6, 2, 3, "bf16", "gelu", 1, "stage"), (700, 1024, 20, 21, 2, 80, "bf16", "gelu", 16, "sum"),
+               (9000, 1024, 5, 6, 2, 3, "bf16", "gelu", 1, "stage"), (2600, 1024, 40, 41, 4, 128, "bf16", "gelu", 1, "stage"),
+               (3501, 512, 40, 41, 4, 128, "f32", "silu", 1, "stage"), (2400, 1024, 40, 41, 4, 128, "bf16", "gelu", 64, "sum"), (700, 1024, 20, 21, 2, 80, "bf16", "gelu", 16, "sum"),
                (2100, 1024, 50, 60, 2, 33, "bf16", "silu", 64, "sum"), (511, 1024, 8, 9, 2, 7, "bf16", "gelu", 1, ""),
                (512, 1024, 50, 60, 1, 11, "bf16", "gelu", 1, "")]
 
