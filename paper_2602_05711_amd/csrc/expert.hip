@@ -578,6 +578,7 @@ struct TokenArgs {
   int d;
   int hk;
   int act;
+  int part;        // token_stage_kernel: slots per partial sum of y (hk: one sum)
   int nchunks;
 };
 
@@ -696,7 +697,10 @@ hipError_t dispatch_dot(int cpl, dim3 grid, hipStream_t st, const DotArgs& a) {
 // One workgroup of four waves per token. The token's slots are taken up to 256 at a time: each wave
 // forms the a of a quarter of them (token row in registers, G u rows in flight, one activation for
 // all of the wave's slots, lane j finishing slot j) and leaves them in LDS; then each wave sums
-// a v over all of them, in slot order, for a quarter of the columns (eight v rows in flight).
+// a v over all of them, in slot order, for a quarter of the columns (eight v rows in flight). PARTS: where
+// launch_accumulate would share the slots out to waves and add their partial rows (sum_split), the same partial sums
+// one after another, so that y has the same bits (and its shorter chains of additions: 400 tokens of 512 slots,
+// d = 1024, y's error against 64 bits 1.6e-7 in sixteen parts, 4.8e-7 in one).
 // Bound by the latency of its gathers (tables that stay in the MALL, one to a few workgroups per
 // compute unit): one launch and no a[] through memory instead of two, and the dots of a token share
 // its row in registers. Against slot_dot and accumulate (their stage, us): 256 tokens of 8 slots,
@@ -710,7 +714,7 @@ hipError_t dispatch_dot(int cpl, dim3 grid, hipStream_t st, const DotArgs& a) {
 // 30.2, 8000 tokens 102 and 84).
 constexpr int64_t kTokenStageShortRows = 2048;  // tokens
 
-template <int CPL, bool BF16, bool FULL>
+template <int CPL, bool BF16, bool FULL, bool PARTS>
 __global__ __launch_bounds__(256) void token_stage_kernel(TokenArgs a) {
   constexpr int EPC = BF16 ? 8 : 4;
   constexpr int G = CPL >= 8 ? 1 : (CPL >= 4 ? 2 : (CPL >= 2 ? 4 : 8));
@@ -745,6 +749,40 @@ __global__ __launch_bounds__(256) void token_stage_kernel(TokenArgs a) {
     for (int q = 0; q < CW; ++q)
 #pragma unroll
       for (int k = 0; k < EPC; ++k) acc[q][k] = 0.0f;
+    // the partial sums before this one, added up; slots from `next` on belong to the following one
+    [[maybe_unused]] float sum[CW][EPC];
+    [[maybe_unused]] int next = a.part;
+    [[maybe_unused]] auto close_part = [&]() {
+#pragma unroll
+      for (int q = 0; q < CW; ++q)
+#pragma unroll
+        for (int k = 0; k < EPC; ++k) {
+          sum[q][k] = next == a.part ? acc[q][k] : sum[q][k] + acc[q][k];
+          acc[q][k] = 0.0f;
+        }
+      next += a.part;
+    };
+    auto add = [&](const uint4 (&row)[CW], float wgt) {
+#pragma unroll
+      for (int q = 0; q < CW; ++q) {
+        const uint4 c = row[q];
+        if constexpr (BF16) {
+          acc[q][0] = fmaf(wgt, bf16_lo(c.x), acc[q][0]);
+          acc[q][1] = fmaf(wgt, bf16_hi(c.x), acc[q][1]);
+          acc[q][2] = fmaf(wgt, bf16_lo(c.y), acc[q][2]);
+          acc[q][3] = fmaf(wgt, bf16_hi(c.y), acc[q][3]);
+          acc[q][4] = fmaf(wgt, bf16_lo(c.z), acc[q][4]);
+          acc[q][5] = fmaf(wgt, bf16_hi(c.z), acc[q][5]);
+          acc[q][6] = fmaf(wgt, bf16_lo(c.w), acc[q][6]);
+          acc[q][7] = fmaf(wgt, bf16_hi(c.w), acc[q][7]);
+        } else {
+          acc[q][0] = fmaf(wgt, __uint_as_float(c.x), acc[q][0]);
+          acc[q][1] = fmaf(wgt, __uint_as_float(c.y), acc[q][1]);
+          acc[q][2] = fmaf(wgt, __uint_as_float(c.z), acc[q][2]);
+          acc[q][3] = fmaf(wgt, __uint_as_float(c.w), acc[q][3]);
+        }
+      }
+    };
     for (int sb = 0; sb < a.hk; sb += kBatch) {
       const int n = a.hk - sb < kBatch ? a.hk - sb : kBatch;
       const int per = (n + 3) / 4;
@@ -789,30 +827,20 @@ __global__ __launch_bounds__(256) void token_stage_kernel(TokenArgs a) {
             for (int q = 0; q < CW; ++q) vr[i][q] = vb[c2[q]];
           }
           __builtin_amdgcn_sched_barrier(0);
+          const int s0 = sb + j0 + j;
+          if (PARTS && s0 == next) close_part();
+          if (PARTS && next < s0 + GV && next < a.hk) {  // a part begins inside the group
 #pragma unroll
-          for (int i = 0; i < GV; ++i) {
-            if (j + i < m) {
-              const float wgt = readlane_f32(av, j + i);
-#pragma unroll
-              for (int q = 0; q < CW; ++q) {
-                const uint4 c = vr[i][q];
-                if constexpr (BF16) {
-                  acc[q][0] = fmaf(wgt, bf16_lo(c.x), acc[q][0]);
-                  acc[q][1] = fmaf(wgt, bf16_hi(c.x), acc[q][1]);
-                  acc[q][2] = fmaf(wgt, bf16_lo(c.y), acc[q][2]);
-                  acc[q][3] = fmaf(wgt, bf16_hi(c.y), acc[q][3]);
-                  acc[q][4] = fmaf(wgt, bf16_lo(c.z), acc[q][4]);
-                  acc[q][5] = fmaf(wgt, bf16_hi(c.z), acc[q][5]);
-                  acc[q][6] = fmaf(wgt, bf16_lo(c.w), acc[q][6]);
-                  acc[q][7] = fmaf(wgt, bf16_hi(c.w), acc[q][7]);
-                } else {
-                  acc[q][0] = fmaf(wgt, __uint_as_float(c.x), acc[q][0]);
-                  acc[q][1] = fmaf(wgt, __uint_as_float(c.y), acc[q][1]);
-                  acc[q][2] = fmaf(wgt, __uint_as_float(c.z), acc[q][2]);
-                  acc[q][3] = fmaf(wgt, __uint_as_float(c.w), acc[q][3]);
-                }
+            for (int i = 0; i < GV; ++i) {
+              if (j + i < m) {
+                if (s0 + i == next) close_part();
+                add(vr[i], readlane_f32(av, j + i));
               }
             }
+          } else {
+#pragma unroll
+            for (int i = 0; i < GV; ++i)
+              if (j + i < m) add(vr[i], readlane_f32(av, j + i));
           }
         }
       }
@@ -822,6 +850,9 @@ __global__ __launch_bounds__(256) void token_stage_kernel(TokenArgs a) {
 #pragma unroll
     for (int q = 0; q < CW; ++q) {
       if (!cv2[q]) continue;
+      if (PARTS && next > a.part)
+#pragma unroll
+        for (int k = 0; k < EPC; ++k) acc[q][k] += sum[q][k];
 #pragma unroll
       for (int k = 0; k < EPC; k += 4)
         yt[(c2[q] * EPC + k) / 4] = make_float4(acc[q][k], acc[q][k + 1], acc[q][k + 2], acc[q][k + 3]);
@@ -898,22 +929,27 @@ __global__ __launch_bounds__(256) void slot_dot_kernel(DotArgs a) {
   if (l < G && p0 + l < a.M) a.a[p0 + l] = gv * activation(a.act, hv);
 }
 
+template <bool BF16, int CPL>
+void launch_stage(dim3 grid, hipStream_t st, const TokenArgs& a) {
+  const bool full = a.nchunks == CPL * kWave, parts = a.part < a.hk;
+#define OMNIMOE_STAGE(F_, P_) \
+  hipLaunchKernelGGL((token_stage_kernel<CPL, BF16, F_, P_>), grid, dim3(256), 0, st, a)
+  if (full && parts) OMNIMOE_STAGE(true, true);
+  else if (full) OMNIMOE_STAGE(true, false);
+  else if (parts) OMNIMOE_STAGE(false, true);
+  else OMNIMOE_STAGE(false, false);
+#undef OMNIMOE_STAGE
+}
+
 template <bool BF16>
 hipError_t dispatch_token_stage(int cpl, dim3 grid, hipStream_t st, const TokenArgs& a) {
-  const bool full = a.nchunks == cpl * kWave;
-#define OMNIMOE_STAGE(C_)                                                                          \
-  do {                                                                                             \
-    if (full) hipLaunchKernelGGL((token_stage_kernel<C_, BF16, true>), grid, dim3(256), 0, st, a); \
-    else hipLaunchKernelGGL((token_stage_kernel<C_, BF16, false>), grid, dim3(256), 0, st, a);     \
-  } while (0)
   switch (cpl) {
-    case 1: OMNIMOE_STAGE(1); break;
-    case 2: OMNIMOE_STAGE(2); break;
-    case 4: OMNIMOE_STAGE(4); break;
-    case 8: OMNIMOE_STAGE(8); break;
-    default: OMNIMOE_STAGE(16); break;
+    case 1: launch_stage<BF16, 1>(grid, st, a); break;
+    case 2: launch_stage<BF16, 2>(grid, st, a); break;
+    case 4: launch_stage<BF16, 4>(grid, st, a); break;
+    case 8: launch_stage<BF16, 8>(grid, st, a); break;
+    default: launch_stage<BF16, 16>(grid, st, a); break;
   }
-#undef OMNIMOE_STAGE
   return hipGetLastError();
 }
 
@@ -941,14 +977,14 @@ hipError_t dispatch_slot_dot(int cpl, dim3 grid, hipStream_t st, const DotArgs& 
 // slots; four otherwise.
 // FULL when each wave's column split is exactly CPL * 64 chunks of the row.
 template <bool BF16>
-hipError_t dispatch_acc_slots(int cpl, int hk, dim3 grid, hipStream_t st, const AccArgs& a) {
+hipError_t dispatch_acc_slots(int cpl, int waves, dim3 grid, hipStream_t st, const AccArgs& a) {
   const bool full = a.nchunks == a.splits * cpl * kWave;
 #define OMNIMOE_ACCS(W_, C_)                                                                    \
   do {                                                                                          \
     if (full) hipLaunchKernelGGL((accumulate_slots_kernel<W_, C_, BF16, true>), grid, dim3(64 * W_), 0, st, a); \
     else hipLaunchKernelGGL((accumulate_slots_kernel<W_, C_, BF16, false>), grid, dim3(64 * W_), 0, st, a);     \
   } while (0)
-  if (cpl <= 2 && hk >= 64) {
+  if (waves == 16) {
     if (cpl == 1) OMNIMOE_ACCS(16, 1);
     else OMNIMOE_ACCS(16, 2);
     return hipGetLastError();
@@ -1068,6 +1104,28 @@ bool slot_dot(const Shape& s) {
           (table <= kMallBytes && s.M <= kSlotDotMallTasks * s.N));
 }
 
+namespace {
+
+// How the routed sum splits its work. Few tokens: each token's row over several waves (whole 64-chunk rows each), and
+// where that still leaves few waves a workgroup per (token, column split), whose `waves` waves take a part of the
+// slots each; their partial rows are added in wave order. (waves 1: the slots one after another.)
+struct SumSplit {
+  int splits;
+  int cpl;
+  int waves;
+};
+SumSplit sum_split(const Shape& s) {
+  const int nchunks = s.bf16 ? s.d / 8 : s.d / 4;
+  const int rows64 = (nchunks + kWave - 1) / kWave;
+  SumSplit f = {1, 0, 1};
+  while (f.splits < rows64 && s.T * f.splits < 1024 && rows64 % (f.splits * 2) == 0) f.splits *= 2;
+  f.cpl = chunks_per_lane((nchunks + f.splits - 1) / f.splits);
+  if (s.T * f.splits < 1024 && s.hk >= 16) f.waves = f.cpl <= 2 && s.hk >= 64 ? 16 : 4;
+  return f;
+}
+
+}  // namespace
+
 bool token_stage(const Shape& s) { return s.T >= 400 || s.T >= 6 * (int64_t)s.hk; }
 
 hipError_t launch_slot_dot(const Shape& s, const void* x, const void* u, const int32_t* idx,
@@ -1109,22 +1167,18 @@ hipError_t launch_accumulate(const Shape& s, const void* v, const int32_t* idx, 
   a.d = s.d;
   a.hk = s.hk;
   a.nchunks = s.bf16 ? s.d / 8 : s.d / 4;
-  // Few tokens: split each token's row over several waves (whole 64-chunk rows each).
-  const int rows64 = (a.nchunks + kWave - 1) / kWave;
-  int splits = 1;
-  while (splits < rows64 && s.T * splits < 1024 && rows64 % (splits * 2) == 0) splits *= 2;
+  const SumSplit f = sum_split(s);
+  const int splits = f.splits, cpl = f.cpl;
   a.splits = splits;
-  const int cpl = chunks_per_lane((a.nchunks + splits - 1) / splits);
-  if (s.T * splits < 1024 && s.hk >= 16) {
-    // still few waves: a workgroup per (token, column split), slots shared by its waves
+  if (f.waves > 1) {
     const int64_t units = s.T * splits;
     const dim3 grid((unsigned)(units < 16384 ? units : 16384));
-    return s.bf16 ? dispatch_acc_slots<true>(cpl, s.hk, grid, st, a)
-                  : dispatch_acc_slots<false>(cpl, s.hk, grid, st, a);
+    return s.bf16 ? dispatch_acc_slots<true>(cpl, f.waves, grid, st, a)
+                  : dispatch_acc_slots<false>(cpl, f.waves, grid, st, a);
   }
   int64_t blocks = (s.T * splits + 3) / 4;
   if (blocks > 16384) blocks = 16384;
-  const bool deep = s.T * rows64 <= kAccDeepMaxRows;
+  const bool deep = s.T * ((a.nchunks + kWave - 1) / kWave) <= kAccDeepMaxRows;
   return s.bf16 ? dispatch_acc<true>(cpl, dim3((unsigned)blocks), st, a, deep)
                 : dispatch_acc<false>(cpl, dim3((unsigned)blocks), st, a, deep);
 }
@@ -1171,6 +1225,8 @@ hipError_t launch_token_stage(const Shape& s, const void* x, const void* u, cons
   a.nchunks = s.bf16 ? s.d / 8 : s.d / 4;
   if (a.nchunks < kWave && s.T >= kTokenStageShortRows)
     return launch_token_centric(s, x, u, v, idx, gates, y, st);
+  const int waves = sum_split(s).waves;
+  a.part = (s.hk + waves - 1) / waves;
   const dim3 grid((unsigned)(s.T < 65536 ? s.T : 65536));
   const int cpl = chunks_per_lane(a.nchunks);
   return s.bf16 ? dispatch_token_stage<true>(cpl, grid, st, a)

@@ -217,7 +217,7 @@ hipError_t launch_slot_dot(const Shape& s, const void* x, const void* u, const i
                            const float* gates, float* abuf, hipStream_t st);
 
 // launch_slot_dot and launch_accumulate in one kernel, a workgroup (or, for many tokens with
-// short rows, a wave) per token, where token_stage(s): the slots summed one after another.
+// short rows, a wave) per token, where token_stage(s): the same dots and sums, bit for bit.
 bool token_stage(const Shape& s);
 hipError_t launch_token_stage(const Shape& s, const void* x, const void* u, const void* v,
                               const int32_t* idx, const float* gates, float* y, hipStream_t st);

@@ -261,13 +261,16 @@ def test_f32_logits(case):
 
 # (T, d, n_rows, n_cols, H, K, dtype, act, one kernel?): the expert stage by tokens in the layer: both sides of its line (400
 # tokens, or six per slot), slots that four waves do not share evenly and more than one batch of 256, rows of one to
-# eight chunks a lane, whole and partial; short rows with one wave per token from 2048 tokens on; tables past 128 MiB on
+# eight chunks a lane, whole and partial; sums of one part, of four and of sixteen (up to 1023 tokens of sixteen slots or
+# 64); short rows with one wave per token from 2048 tokens on; tables past 128 MiB on
 # both sides of six tasks per expert.
 STAGE_CASES = [(48, 64, 16, 17, 1, 8, "f32", "gelu", True), (47, 64, 16, 17, 1, 8, "f32", "gelu", False),
                (400, 520, 12, 13, 3, 13, "f32", "silu", True), (399, 512, 30, 40, 3, 27, "bf16", "gelu", False),
                (401, 1024, 20, 21, 2, 150, "bf16", "gelu", True), (2048, 200, 10, 10, 2, 5, "bf16", "gelu", True),
                (2047, 200, 10, 10, 2, 5, "bf16", "silu", True), (500, 2048, 9, 10, 5, 3, "bf16", "gelu", True),
                (430, 4096, 5, 6, 1, 3, "f32", "gelu", True), (450, 2056, 7, 9, 2, 3, "bf16", "gelu", True),
+               (500, 512, 20, 21, 4, 16, "bf16", "gelu", True), (1023, 520, 12, 13, 2, 8, "f32", "silu", True),
+               (1024, 520, 12, 13, 2, 8, "f32", "silu", True), (100, 1024, 20, 21, 1, 16, "f32", "gelu", True),
                (600, 4088, 128, 129, 2, 82, "bf16", "gelu", True), (608, 4088, 128, 129, 2, 82, "bf16", "gelu", False)]
 
 
@@ -283,8 +286,12 @@ def test_token_stage_layer(case):
     idx = torch.empty((T, H, K), dtype=torch.int32, device="cuda")
     g = torch.empty((T, H, K), device="cuda")
     P.omnimoe_layer_forward(D, dev["x"], dev["keys_row"], dev["keys_col"], dev["u"], dev["v"], y, idx, g)
-    y_tc = torch.full((T, d), float("nan"), device="cuda")
-    P.omnimoe_expert_forward_token_centric(D, dev["x"], dev["u"], dev["v"], idx, g, y_tc)
+    # the stage on its own on the layer's routing: the dots and the sum in kernels of their own
+    perm, act_, off, na = (torch.empty(n, dtype=torch.int32, device="cuda")
+                           for n in (w.M, min(w.M, w.N), min(w.M, w.N) + 1, 1))
+    P.omnimoe_schedule(D, idx, perm, act_, off, na)
+    y_ef = torch.full((T, d), float("nan"), device="cuda")
+    P.omnimoe_expert_forward(D, dev["x"], dev["u"], dev["v"], idx, g, perm, y_ef)
     torch.cuda.synchronize()
     f = {k: synth.as_f32(v) for k, v in inp.items()}
     gi, gg = idx.cpu().numpy(), g.cpu().numpy()
@@ -293,8 +300,8 @@ def test_token_stage_layer(case):
     # fp32 sums of exact products: Higham's bounds through the activation (as for the routed sum above)
     got = y.cpu().numpy()
     assert np.all(np.abs(got.astype(np.float64) - ref) <= grouped_gap_bound(f, gi, gg, d, dsc.act))
-    if one:  # the same dots and the same slot order
-        assert np.array_equal(got.view(np.uint8), y_tc.cpu().numpy().view(np.uint8))
+    # the same dots and the same partial sums, with a workgroup per token or without
+    assert np.array_equal(got.view(np.uint8), y_ef.cpu().numpy().view(np.uint8))
 
 
 # (T, d, n_rows, n_cols, H, K, dtype, act, group size, swept): the expert stage in sweeps in the layer (at least 512 tokens, two
