@@ -567,8 +567,8 @@ __global__ __launch_bounds__(256) void route_keysum_kernel(RouteArgs a, int64_t 
     const raw* const X = (const raw*)a.x + (half ? a.col0 / 4 : 0) + qc;
     const int64_t xq = a.d / 4;
     f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
-    for (int base = b; base < e; base += kWave) {
-      const int n = e - base < kWave ? e - base : kWave;
+    for (int64_t base = b; base < e; base += kWave) {  // (the step past the last pick may leave 32 bits)
+      const int n = (int)(e - base < kWave ? e - base : kWave);
       const int2 pk = a.picks[base + (l < n ? l : n - 1)];
       const int tl = clamp_id(pk.x, a.T);
       for (int j0 = 0; j0 < n; j0 += G) {

@@ -236,6 +236,33 @@ def test_route_backward_picks(case):
         assert np.array_equal(x0.view(np.uint8), x1.view(np.uint8))
 
 
+def test_route_backward_one_half_at_a_time():
+    """2^30 tasks, whose picks of both halves 32 bits do not number: each half in a round of its own. Every token picks every
+    cell of the grid; the weights are whole numbers, zero but for a few tokens, so that every sum is exact."""
+    T, n, dk = 1 << 18, 64, 8
+    w = synth.Workload("half", T=T, d=2 * dk, n_rows=n, n_cols=n, d_key=dk, H=1, K=n * n)
+    say(f"[route backward] {w.M} tasks")
+    rng = np.random.default_rng(3)
+    x = torch.from_numpy(rng.integers(-4, 5, (T, 2 * dk)).astype(np.float32)).to(torch.bfloat16)
+    kr, kc = (torch.from_numpy(rng.integers(-4, 5, (1, n, dk)).astype(np.float32)).to(torch.bfloat16) for _ in range(2))
+    order = torch.from_numpy(rng.permutation(n * n).astype(np.int32))
+    idx = order.cuda().repeat(T, 1).view(T, 1, n * n)
+    slot = torch.from_numpy(rng.integers(-3, 4, n * n).astype(np.float32))
+    tok = torch.zeros(T)
+    tok[torch.tensor([0, 1, 77777, T // 2, T - 2, T - 1])] = torch.tensor([1.0, -2.0, 3.0, 1.0, 2.0, -1.0])
+    ds = (tok.cuda()[:, None] * slot.cuda()[None]).view(T, 1, n * n)
+    dx = torch.zeros((T, 2 * dk), device="cuda")
+    dkr, dkc = (torch.full((1, n, dk), float("nan"), device="cuda") for _ in range(2))
+    P.omnimoe_route_backward(B.make_desc(w), x.cuda(), kr.cuda(), kc.cuda(), idx, ds, dx, dkr, dkc)
+    torch.cuda.synchronize()
+    for half, got, keys in ((order.long() // n, dkr, kr), (order.long() % n, dkc, kc)):
+        q = 0 if got is dkr else dk
+        per_key = torch.zeros(n).scatter_add_(0, half, slot)
+        assert torch.equal(got[0].cpu(), per_key[:, None] * (tok @ x[:, q:q + dk].float())[None])
+        want = tok[:, None] * (per_key @ keys[0].float())[None]
+        assert torch.equal(dx[:, q:q + dk].cpu(), want)
+
+
 # (T, d, d_key, n_rows, n_cols, H, query): fp32 logits on tiles of 64 x 64 with k steps of 32: one k step and several, whole and
 # partial, tokens and keys at a tile's edge and past it.
 F32_LOGIT_CASES = [(1, 16, 8, 1, 3, 1, "split"), (64, 64, 32, 32, 64, 2, "split"), (65, 80, 40, 64, 65, 1, "split"),
