@@ -24,8 +24,6 @@
 namespace omnimoe {
 namespace {
 
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-
 struct BwdArgs {
   const void* x;
   const void* u;
@@ -61,18 +59,6 @@ struct BwdArgs {
 
 __device__ __forceinline__ int clamp_id(int v, int64_t n) {
   return v < 0 ? 0 : (v >= n ? (int)(n - 1) : v);
-}
-
-// Element k (0 .. EPC-1) of a stored 16-byte chunk, as fp32.
-template <bool BF16>
-__device__ __forceinline__ float chunk_elem(const uint4& c, int k) {
-  if constexpr (BF16) {
-    const uint32_t w = k < 2 ? c.x : (k < 4 ? c.y : (k < 6 ? c.z : c.w));
-    return (k & 1) ? bf16_hi(w) : bf16_lo(w);
-  } else {
-    const uint32_t w = k == 0 ? c.x : (k == 1 ? c.y : (k == 2 ? c.z : c.w));
-    return __uint_as_float(w);
-  }
 }
 
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
@@ -677,7 +663,7 @@ void launch_bwd(hipStream_t st, const BwdArgs& a) {
 #undef OMNIMOE_BWD
 }
 
-// cpl: 256-element pieces of a row, rounded up to a power of two (at most 16: d <= 4096).
+// cpl: 256-element pieces of a row, rounded up to a power of two (at most 16: d <= 4096; 8 in fp32: d <= 2048).
 template <bool BF16>
 hipError_t dispatch_bwd(int cpl, hipStream_t st, const BwdArgs& a) {
   switch (cpl) {
@@ -685,7 +671,12 @@ hipError_t dispatch_bwd(int cpl, hipStream_t st, const BwdArgs& a) {
     case 2: launch_bwd<BF16, 2, 4>(st, a); break;
     case 4: launch_bwd<BF16, 4, 2>(st, a); break;
     case 8: launch_bwd<BF16, 8, 1>(st, a); break;
-    case 16: launch_bwd<BF16, 16, 1>(st, a); break;
+    case 16:
+      if constexpr (BF16) {
+        launch_bwd<BF16, 16, 1>(st, a);
+        break;
+      }
+      [[fallthrough]];
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
