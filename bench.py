@@ -63,6 +63,41 @@ def algorithmic_work(w, n_active):
     }
 
 
+def kernel_work(w, n_active, path):
+    """algorithmic_work on the kernels that the layer runs (omnimoe_layer_kernels' flags), and the groups that it does not
+    launch for this shape, with the reason: their time is that of no work at all."""
+    from paper_2602_05711_amd import binding as B
+
+    work = algorithmic_work(w, n_active)
+    s_in = 2 if w.bf16 else 4
+    absent = {}
+    if not path & (B.PATH_SCHEDULE | B.PATH_DENSE_DOT | B.PATH_SWEEP_STAGE):
+        absent["schedule"] = "not formed (slot-order dot)"
+    if path & B.PATH_SELECT_DOT:
+        absent["expert_dot"] = "formed by the selection kernel"
+        work["select"] = ("hbm", work["select"][1] + work["expert_dot"][1])
+    if path & B.PATH_TOKEN_STAGE:
+        # u, x, v and idx and gates in, y out: no a through memory
+        absent["expert_dot"] = "formed with the routed sum"
+        work["accumulate"] = ("hbm", work["accumulate"][1] + (float(n_active) + w.T) * w.d * s_in)
+    if path & B.PATH_SWEEP_STAGE:
+        # each token's order: idx in, the (expert, slot) list out
+        work["schedule"] = ("hbm", 12.0 * w.M)
+    if path & B.PATH_SWEEP_SUM:
+        # the order of the sum counts with it: idx and a in, the (expert, a) list out and in again
+        work["accumulate"] = ("hbm", work["accumulate"][1] + 16.0 * w.M)
+    # Products dense over all experts (Eq. 14 with a single group) are MFMA GEMMs: priced by the
+    # FLOP they perform, 2 T N d each (the expert dimension padded to the split width).
+    dense_flop = 2.0 * w.T * w.N * w.d
+    if path & B.PATH_DENSE_SUM:
+        work["accumulate"] = ("mfma", dense_flop)
+    if path & B.PATH_DENSE_DOT:
+        work["expert_dot"] = ("mfma", dense_flop)
+        # the selection-mask pass: idx and gates in; mask, prefix counts and sorted gates out
+        work["schedule"] = ("hbm", 8.0 * w.M + 8.0 * w.T * ((w.N + 31) // 32) + 4.0 * w.M)
+    return work, absent
+
+
 def load_traffic(kernel, workload):
     """HBM bytes per launch from the committed rocprofv3 counter summary, or None when the
     kernel's sources changed since the counters were taken."""
@@ -584,31 +619,14 @@ def main():
             args, w, desc, d_in, dev, idx, g, y, stream, per, ms_step, ev0, ev1,
             (perm, off, na, n_active))
 
-    work = algorithmic_work(w, n_active)
-    path = P.omnimoe_layer_path(desc)
-    # Kernel groups the layer does not launch for this shape: no schedule (slot-order dot), or
-    # a dot formed by the selection kernel, whose time and bytes then count under "select".
-    absent = {}
-    if not path & (B.PATH_SCHEDULE | B.PATH_DENSE_DOT):
-        absent["schedule"] = "not formed (slot-order dot)"
-    if path & B.PATH_SELECT_DOT:
-        absent["expert_dot"] = "formed by the selection kernel"
-        work["select"] = ("hbm", work["select"][1] + work["expert_dot"][1])
-    # Products dense over all experts (Eq. 14 with a single group) are MFMA GEMMs: priced by the
-    # FLOP they perform, 2 T N d each (the expert dimension padded to the split width).
-    dense_flop = 2.0 * w.T * w.N * w.d
-    if path & B.PATH_DENSE_SUM:
-        work["accumulate"] = ("mfma", dense_flop)
-    if path & B.PATH_DENSE_DOT:
-        work["expert_dot"] = ("mfma", dense_flop)
-        # the selection-mask pass: idx and gates in; mask, prefix counts and sorted gates out
-        work["schedule"] = ("hbm", 8.0 * w.M + 8.0 * w.T * ((w.N + 31) // 32) + 4.0 * w.M)
+    path = P.omnimoe_layer_kernels(desc)
+    work, absent = kernel_work(w, n_active, path)
     kernels = {}
     for k, (bound, amount) in work.items():
         if k in absent:
             kernels[k] = {"absent": absent[k], "ms": per[k]}
             continue
-        t_s = max(per[k], 1e-6) * 1e-3  # a group that launches nothing takes no time
+        t_s = per[k] * 1e-3
         if bound == "hbm":
             ach = amount / t_s / 1e9
             kernels[k] = {"bound": "hbm", "ms": per[k], "achieved": ach, "unit": "GB/s",
@@ -684,12 +702,16 @@ def main():
         "group_rows_second_product": group_rows,
         "accumulate_contribution_rows": contrib,
         "n_active": n_active, "eta": w.M / max(1, n_active), "routing": routing,
-        "schedule_share": per["schedule"] / sum(per.values()) if path & B.PATH_SCHEDULE else 0.0,
+        "schedule_share": per["schedule"] / sum(per.values()) if path & (
+            B.PATH_SCHEDULE | B.PATH_SWEEP_STAGE) else 0.0,
         "layer_path": {"schedule": bool(path & B.PATH_SCHEDULE),
                        "grouped": bool(path & B.PATH_GROUPED),
                        "select_forms_dot": bool(path & B.PATH_SELECT_DOT),
                        "dense_routed_sum": bool(path & B.PATH_DENSE_SUM),
-                       "dense_expert_dot": bool(path & B.PATH_DENSE_DOT)},
+                       "dense_expert_dot": bool(path & B.PATH_DENSE_DOT),
+                       "token_stage": bool(path & B.PATH_TOKEN_STAGE),
+                       "swept_stage": bool(path & B.PATH_SWEEP_STAGE),
+                       "swept_sum": bool(path & B.PATH_SWEEP_SUM)},
         "kernels": kernels,
     }
     s = json.dumps(line)
