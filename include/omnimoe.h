@@ -288,8 +288,10 @@ omnimoe_status omnimoe_expert_backward(const omnimoe_layer_desc* desc, const voi
  *   dx        [T, d] fp32 in/out           adds sum over t's tasks of dscores_p keys_row[h, i_p]
  *                                          (columns 0:d_key) and dscores_p keys_col[h, j_p]
  *                                          (columns c0:c0+d_key); c0 = d_key (split) or 0
- * Tasks are sorted by sub-key with the schedule's radix sort and each sub-key's gradient is
- * summed over its tasks in task order, so the result is the same on every run. d_key <= 4096
+ * Of the tasks of one (token, head) row, those in a block of sixteen slots (fewer for K < 16) that
+ * share a sub-key are merged into one pick, their dscores added in slot order; a counting pass
+ * orders the picks by sub-key, and each sub-key's gradient is summed over its picks, tokens
+ * ascending. There are no atomics on the sums, so the result is the same on every run. d_key <= 4096
  * (bf16) or 2048 (fp32), else OMNIMOE_ERR_UNSUPPORTED. Workspace: OMNIMOE_STAGE_ROUTE_BACKWARD
  * bytes. */
 omnimoe_status omnimoe_route_backward(const omnimoe_layer_desc* desc, const void* x,
@@ -315,8 +317,9 @@ omnimoe_status omnimoe_route_backward(const omnimoe_layer_desc* desc, const void
  * With at least 512 tokens, two tasks per expert and tables of at most 256 MiB whose rows are 2, 4
  * or 8 KiB, every token's tasks are put in one order of the experts instead and swept by all tokens
  * together (OMNIMOE_KERNEL_SCHEDULE times that ordering): the sums run in another fixed order, so y
- * matches omnimoe_expert_forward's to fp32 rounding; with groups of B > 1 this holds for the routed
- * sum. With one head, K >= N / 64 and group_size 1,
+ * matches omnimoe_expert_forward's to fp32 rounding, and a token's y may differ in its last bits
+ * between a call of fewer and one of more tokens than that; with groups of B > 1 this holds for the
+ * routed sum. With one head, K >= N / 64 and group_size 1,
  * both products run dense over all experts (Eq. 14 with a single group): x . u for every
  * (token, expert) pair, gate and activation kept at the selected pairs (a_p rounded to bf16),
  * then y = A V; no schedule is formed. Workspace:

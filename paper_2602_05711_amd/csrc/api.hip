@@ -97,8 +97,12 @@ bool layer_grouped(const Shape& s) { return s.B > 1 && grouped_supported(s); }
 // Where the expert-major order saves no memory traffic (a decode step; at most one task per two
 // experts; or a u table that fits in the MALL) the layer takes the slot-order dot and forms no
 // schedule. With at least kSelectDotMinRows (token, head) rows the selection kernel forms that
-// dot itself; with fewer, a wave per row would fetch its K u rows four at a time, while the
-// separate dot kernel fetches all of them at once (one decoded token: 19.1 against 22.1 us).
+// dot itself. The line was measured when a wave took a row and fetched its K u rows four at a time (one decoded
+// token 22.1 us against 19.1 with the separate dot kernel, which fetches all of them at once). With the workgroup
+// per row that launch_select_dot now takes up to 512 rows the fused form is the faster below the line as well
+// (layer call, separate and fused, us: 1024^2 experts of d = 2048, 8 rows 19.2 and 17.9, 64 rows 23.4 and 21.8, 192
+// rows 24.8 and 22.7; one head, 192 rows 21.5 and 21.6, 248 rows 22.9 and 23.3; 256^2 of d = 512, 64 rows 15.9 and
+// 14.3); the line is where it was.
 constexpr int64_t kSelectDotMinRows = 256;
 // Up to this many tasks the sort by expert is one launch, as cheap as the flag pass and scan
 // that replace it above (launch_group_schedule).
@@ -111,7 +115,11 @@ constexpr int32_t kPathReported = OMNIMOE_PATH_TOKEN_STAGE - 1;
 // tokens) 78 and 84, 2048 tokens 157 and 132, 16384 tokens 1024 and 785; K = 512: 400 tokens 130 and 135,
 // 512 tokens 152 and 137, 1024 tokens 298 and 199, 4096 tokens 972 and 582. 64 slots on 6 10^4 experts: 1024
 // tokens 44 and 47, 2048 tokens 82 and 75; on 10^4: 1024 tokens 37 and 27; on 4 10^4 of d = 2048:
-// 1024 tokens 83 and 73.
+// 1024 tokens 83 and 73. Whole layer, the kernels before the sweeps and the sweeps: rows of 8 KiB (128^2 of d = 4096, 32
+// slots) 1024 tokens 105 and 79, 4096 tokens 382 and 248; fp32 (320^2 of d = 512, 64 slots) 4096 tokens 286 and 197, (64^2
+// of d = 1024, 16 slots) 512 tokens 33 and 27, 4096 tokens 95 and 54, (170^2 of d = 2048, 64 slots) 1024 tokens 230 and 147.
+// Skewed picks (sub-key logits that fall with the logarithm of a rank), K = 512 on 320^2 of d = 1024: 512 tokens 334 and
+// 170, 4096 tokens 933 and 598; 10^4 of d = 1024, 64 slots: 512 tokens 43 and 38, 4096 tokens 112 and 93.
 bool sweep_pays(const Shape& s) {
   return omnimoe::sweepable(s) && s.T >= 512 && s.M >= 2 * s.N;
 }

@@ -143,7 +143,10 @@ __device__ __forceinline__ int64_t segment_of(const int32_t* offsets, int64_t n,
 // instead of saving 0.6). Measured at the training shape, token pass and expert pass 8.73 ms before, this pass
 // and the routed sum 7.02 ms (two experts per wave; four 7.03, eight 7.32; two tasks in flight instead of
 // one 7.49; four waves sharing an expert's columns 7.27); 4093 tokens, 2^16 experts of d = 512: 236 ->
-// 156 us (G = 4; 161 with two in flight, 169 with six).
+// 156 us (G = 4; 161 with two in flight, 169 with six). 2048 tokens of 32 tasks, 2^14 experts of d = 4096: 461 -> 428. With
+// about one task per active expert the sum over dx reads most u rows a second time (2048 tokens at the training
+// shape, 231k experts of 1.1 tasks: 1354 -> 1409 us, 5.7 GB and 1.07 GB at 4.8 and 5.5 TB/s); with fewer tokens the
+// former pass by tokens had too few waves (512 tokens 441 -> 350, 64 tokens 168 -> 52).
 //
 // A wave forms about one task a microsecond, so an expert that many tokens pick would be walked by one wave
 // while the chip idles. A segment of more than one piece of tasks (16, or M / 2048 where that is more: at most
