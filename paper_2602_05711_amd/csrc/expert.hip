@@ -700,7 +700,8 @@ hipError_t dispatch_dot(int cpl, dim3 grid, hipStream_t st, const DotArgs& a) {
 // a v over all of them, in slot order, for a quarter of the columns (eight v rows in flight). PARTS: where
 // launch_accumulate would share the slots out to waves and add their partial rows (sum_split), the same partial sums
 // one after another, so that y has the same bits (and its shorter chains of additions: 400 tokens of 512 slots,
-// d = 1024, y's error against 64 bits 1.6e-7 in sixteen parts, 4.8e-7 in one).
+// d = 1024, y's error against 64 bits 1.6e-7 in sixteen parts, 4.8e-7 in one; the layer of 600 tokens of 64 slots, d =
+// 512, takes 30.9 us in sixteen parts and 30.1 in one, of 1000 tokens of 39 slots, d = 520 fp32, 50.4 and 50.3).
 // Bound by the latency of its gathers (tables that stay in the MALL, one to a few workgroups per
 // compute unit): one launch and no a[] through memory instead of two, and the dots of a token share
 // its row in registers. Against slot_dot and accumulate (their stage, us): 256 tokens of 8 slots,
@@ -751,13 +752,18 @@ __global__ __launch_bounds__(256) void token_stage_kernel(TokenArgs a) {
       for (int k = 0; k < EPC; ++k) acc[q][k] = 0.0f;
     // the partial sums before this one, added up; slots from `next` on belong to the following one
     [[maybe_unused]] float sum[CW][EPC];
+    if (PARTS)
+#pragma unroll
+      for (int q = 0; q < CW; ++q)
+#pragma unroll
+        for (int k = 0; k < EPC; ++k) sum[q][k] = -0.0f;  // (changes no first addend, not even a zero)
     [[maybe_unused]] int next = a.part;
     [[maybe_unused]] auto close_part = [&]() {
 #pragma unroll
       for (int q = 0; q < CW; ++q)
 #pragma unroll
         for (int k = 0; k < EPC; ++k) {
-          sum[q][k] = next == a.part ? acc[q][k] : sum[q][k] + acc[q][k];
+          sum[q][k] += acc[q][k];
           acc[q][k] = 0.0f;
         }
       next += a.part;
@@ -850,7 +856,7 @@ __global__ __launch_bounds__(256) void token_stage_kernel(TokenArgs a) {
 #pragma unroll
     for (int q = 0; q < CW; ++q) {
       if (!cv2[q]) continue;
-      if (PARTS && next > a.part)
+      if (PARTS)
 #pragma unroll
         for (int k = 0; k < EPC; ++k) acc[q][k] += sum[q][k];
 #pragma unroll
